@@ -32,9 +32,11 @@ __device__ __forceinline__ double rcbrt_f64(double r) {
 
 // ---------------------------------------------------------------------------
 // Background: a(t) of eq. scalefac2 (t = lookback time), 1/a and da/dt.
-// a = (ratio sinh^2 u)^(1/3) comes as r (r^(-1/3))^2, which gives 1/a and 1/a^2 with it: no
-// division by a.  The integration of a ray is one chain of dependent FP64 operations per
-// stage, whose length bounds the small launches.
+// a = (ratio sinh^2 u)^(1/3) comes as r (r^(-1/3))^2, which gives 1/a with it: no division by a.  Both are
+// corrected by their own remainders, r - a^3 (with a^2 in two parts) and 1 - a (1/a), and so rounded like a cube
+// root and a division (uncorrected, a was off by up to 3.7 x 2^-53).
+// The integration of a ray is one chain of dependent FP64 operations per stage, whose length bounds the small
+// launches; the corrections lengthen it by six of them (point lens, 4900 stages: 3.70 -> 3.81 ms).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void scale_factor(const DevCosmo& c, double t, double& a, double& inv_a, double& adot) {
   const double rate = 1.5 * c.sqrt_ol * c.H0;
@@ -43,9 +45,11 @@ __device__ __forceinline__ void scale_factor(const DevCosmo& c, double t, double
   const double ie = recip_f64(e);
   const double sh = 0.5 * (e - ie), ch = 0.5 * (e + ie);
   const double a3 = c.ratio * sh * sh;
-  inv_a = rcbrt_f64(a3);
+  const double y = rcbrt_f64(a3), y2 = y * y, b = a3 * y2;
+  const double b2 = b * b, low = fma(b, b, -b2);
+  a = fma(fma(-low, b, fma(-b2, b, a3)), y2 * (1.0 / 3.0), b);
+  inv_a = fma(y, fma(-a, y, 1.0), y);
   const double inv_a2 = inv_a * inv_a;
-  a = a3 * inv_a2;
   // a^3 = ratio sh^2  =>  3 a^2 da/dt = -2 ratio sh ch rate
   adot = -(2.0 / 3.0) * rate * c.ratio * sh * ch * inv_a2;
 }
