@@ -78,6 +78,13 @@ int plan_count(bool fp64);
 rt_plan_info plan_info(bool fp64, int id);
 bool plan_few(bool fp64, int id);    // a plan for launches of few rays (trace_few_kernel)
 constexpr int64_t kSmallSet = 63;    // sets of at most so many particles are summed in FP64 in every precision
+// The plan of few rays without a particle split (kRayPlanRays rays to a workgroup of one wavefront, sets staged in
+// kRayPlanTile particles): its kernel for occupancy queries, and its launch.  It is compiled with rt_pm.hip, whose
+// loops keep the constants of exp and its like in registers: this kernel has room for them, and a point lens's 4900 stages
+// take 4.0 ms where they are formed anew in each, 3.8 where they are kept.  rt_kernels.hip's kernels have none (build.py).
+constexpr int kRayPlanRays = 64, kRayPlanTile = 64;
+const void* trace_ray_fn();
+hipError_t launch_trace_ray(const TraceParams& p, int grid, hipStream_t s);
 hipError_t plan_occupancy(bool fp64, int id, int* blocks_per_cu);
 hipError_t launch_trace(bool fp64, int id, const TraceParams& p, int grid, hipStream_t s);
 

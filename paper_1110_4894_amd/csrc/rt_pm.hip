@@ -27,6 +27,7 @@
 #include <cmath>
 #include <cstdint>
 
+#include "rt_direct.h"
 #include "rt_geodesic.h"
 #include "rt_internal.h"
 
@@ -1206,6 +1207,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 inline unsigned blocks_for(int64_t count, int threads) { return (unsigned)((count + threads - 1) / threads); }
 
 }  // namespace
+
+const void* trace_ray_fn() { return (const void*)&trace_few_kernel<kRayPlanRays, 1, 1, kRayPlanTile>; }
+
+hipError_t launch_trace_ray(const TraceParams& p, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((trace_few_kernel<kRayPlanRays, 1, 1, kRayPlanTile>), dim3(grid), dim3(64), 0, s, p);
+  return hipGetLastError();
+}
 
 int64_t pm_workspace_bytes(int n, int periodic) {
   const int64_t M = periodic ? (int64_t)n : 2 * (int64_t)n;
