@@ -92,7 +92,7 @@ __global__ void pm_cic_kernel(const double* __restrict__ xyzm, int64_t np, doubl
 // fill an eighth of the padded grid and an eighth of the results is kept.  So: two real lines share a
 // complex one; only M / 2 + 1 points of the last axis are held; lines that are zero, or not
 // wanted, are left out; transforming the first axis, multiplying and transforming back is
-// one kernel; and one quarter-size transform of phi + i d/dx gives all four kernels, which are real
+// one kernel; and one quarter-size transform of phi + i len d/dx gives all four kernels, which are real
 // after it (P, S) and permutations of each other.
 // Bound: passes through LDS and HBM, about 80 B per point of the padded grid; nine full complex transforms of the
 // padded grid, one line per workgroup, moved about 1100 B a point, 16 B at a time on two axes: 110 ms for
@@ -303,11 +303,14 @@ __global__ __launch_bounds__(kFftThreads) void pm_fft_mid_kernel(Fft f, const do
   }
 }
 
-// The Plummer kernels of eq. psi and eq. derivs on one octant of displacements, value phi + i d/dx,
+// The Plummer kernels of eq. psi and eq. derivs on one octant of displacements, value phi + i len d/dx,
 // even in the last two axes: mirrored and transformed along the last one, c [i][j][k], i, j, k <= n.
 // (Displacement n is met by no pair of nodes: the odd part is 0 there.)
+// len, a power of two, brings d/dx to phi's size: the two share their rounding, which without it is that of
+// the larger for both, i.e. depends on the unit of length (phi off by 5e-13 of its largest value at h = 1e-5, the
+// derivatives by 3e-14 at h = 20).
 __global__ __launch_bounds__(kFftThreads) void pm_kernel_last_kernel(Fft f, int n, double h, double eps2, double G,
-                                                                     double2* c) {
+                                                                     double len, double2* c) {
   __shared__ double2 b[kFftSlots];
   const int m = n + 1;
   const int64_t l0 = (int64_t)blockIdx.x * f.L, n_lines = (int64_t)m * m;
@@ -321,7 +324,7 @@ __global__ __launch_bounds__(kFftThreads) void pm_kernel_last_kernel(Fft f, int 
       const double dx = i * h, dy = j * h, dz = k * h;
       const double r2 = dx * dx + dy * dy + dz * dz + eps2;
       const double k1 = r2 > 0.0 ? 1.0 / sqrt(r2) : 0.0;
-      v = make_double2(-G * k1, i < n ? G * dx * (k1 * k1 * k1) : 0.0);
+      v = make_double2(-G * k1, i < n ? len * (G * dx * (k1 * k1 * k1)) : 0.0);
     }
     b[fft_at(f, p, line)] = v;
   }
@@ -353,11 +356,11 @@ __global__ __launch_bounds__(kFftThreads) void pm_kernel_mid_kernel(Fft f, int n
   }
 }
 
-// The same along the first axis, where d/dx is odd: phi + i d/dx transforms to P + S, P even and S
+// The same along the first axis, where d/dx is odd: phi + i len d/dx transforms to P + len S, P even and S
 // odd, both real (the transform of d/dx is -i S).  ps [i][j][k] = (P, S); sz [j][k][i] = S(i; j, k), i.e.
-// the kernel of the axis in the last place.  scale: 1 / M^3, a power of two.
+// the kernel of the axis in the last place.  scale: 1 / M^3, a power of two; inv_len: 1 / len.
 __global__ __launch_bounds__(kFftThreads) void pm_kernel_first_kernel(Fft f, int n, const double2* c, double scale,
-                                                                      double2* ps, double* sz) {
+                                                                      double inv_len, double2* ps, double* sz) {
   __shared__ double2 b[kFftSlots];
   const FftTile tile = fft_tile();
   const int m = n + 1, k0 = tile.x * f.L;
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(kFftThreads) void pm_kernel_first_kernel(Fft f, int
     const int line = e & (f.L - 1), i = e >> f.logL, k = k0 + line;
     if (k >= m) continue;
     const double a = b[fft_at(f, fft_rev(f, i), line)].x, z = b[fft_at(f, fft_rev(f, (f.M - i) & (f.M - 1)), line)].x;
-    const double S = 0.5 * scale * (a - z);
+    const double S = 0.5 * scale * (a - z) * inv_len;
     ps[i * mm + j * m + k] = make_double2(0.5 * scale * (a + z), S);
     sz[(j * m + k) * m + i] = S;
   }
@@ -487,38 +490,38 @@ __global__ __launch_bounds__(kFftThreads) void pm_ifft_mid_kernel(Fft f, FourOut
   }
 }
 
-// Back along the last axis to real values, quantities 2 z and 2 z + 1 as one complex line (z = blockIdx.z):
-// rows [i][j] of pitch rows_pitch M-rows, j < n, to fields[q][(i n + j) n + k], k < n.
+// Back along the last axis to real values, two lines of one quantity (blockIdx.z) as one complex line (neighbours
+// of one unit: they share their rounding): lines (i, j), j < n, of planes of `rows` rows, to
+// fields[q][(i n + j) n + k], k < n.
 __global__ __launch_bounds__(kFftThreads) void pm_ifft_real_kernel(Fft f, FourOut in, int rows, int n, int nk,
                                                                    double* fields) {
   __shared__ double2 b[kFftSlots];
-  const int64_t l0 = (int64_t)blockIdx.x * f.L, n_lines = (int64_t)n * n;
-  const double2 *__restrict__ X = in.q[2 * blockIdx.z], *__restrict__ Y = in.q[2 * blockIdx.z + 1];
+  const int64_t l0 = (int64_t)blockIdx.x * 2 * f.L, n_lines = (int64_t)n * n;   // (an even number)
+  const double2* __restrict__ X = in.q[blockIdx.z];
 #pragma unroll
   for (int r = 0; r < kFftMine; ++r) {
     const int e = threadIdx.x + r * kFftThreads, k = e & (f.M - 1), line = e >> f.logM;
-    const int64_t l = l0 + line;
+    const int64_t l = l0 + 2 * line;
     double2 v = make_double2(0.0, 0.0);
     if (l < n_lines) {
       const int64_t i = l / n, j = l - i * n;
-      const int ak = k < nk ? k : f.M - k;
-      const double2 x = X[(i * rows + j) * nk + ak], y = Y[(i * rows + j) * nk + ak];
-      v = k < nk ? make_double2(x.x - y.y, x.y + y.x) : make_double2(x.x + y.y, y.x - x.y);   // X + i Y, conj X + i conj Y
+      const int64_t at = (i * rows + j) * nk + (k < nk ? k : f.M - k);
+      const double2 x = X[at], y = X[at + nk];
+      v = k < nk ? make_double2(x.x - y.y, x.y + y.x) : make_double2(x.x + y.y, y.x - x.y);   // x + i y, conj x + i conj y
     }
     b[fft_at(f, fft_rev(f, k), line)] = v;
   }
   __syncthreads();
   fft_inverse(f, b);
-  const int64_t n3 = n_lines * n;
-  double *o0 = fields + 2 * blockIdx.z * n3, *o1 = o0 + n3;
+  double* o = fields + blockIdx.z * n_lines * n;
 #pragma unroll
   for (int r = 0; r < kFftMine; ++r) {
     const int e = threadIdx.x + r * kFftThreads, k = e & (f.M - 1), line = e >> f.logM;
-    const int64_t l = l0 + line;
+    const int64_t l = l0 + 2 * line;
     if (l < n_lines && k < n) {
       const double2 v = b[fft_at(f, k, line)];
-      o0[l * n + k] = v.x;
-      o1[l * n + k] = v.y;
+      o[l * n + k] = v.x;
+      o[(l + 1) * n + k] = v.y;
     }
   }
 }
@@ -1261,11 +1264,16 @@ hipError_t launch_pm_build(const double* xyzm, int64_t np, double eps, const dou
     ps = mass + half;
     const int64_t mm = (int64_t)nk * nk;
     double2* c = ws;
+    // phi / (d phi / dx) in the root mean square over the grid, from e = the larger of spacing and softening to R =
+    // its side: 1/r over it falls to 1/R, x/r^3 to 1/sqrt(e R^3), and for a softening beyond the side to R/e^2
+    const double e = h > eps ? h : eps, R = n * h;
+    const double ratio = sqrt(e) * sqrt(R) * (e > R ? (e / R) * sqrt(e / R) : 1.0);
+    const double len = ratio > 1e-100 && ratio < 1e100 ? exp2(rint(log2(ratio))) : 1.0;
     sz = reinterpret_cast<double*>(ps + mm * nk);
-    hipLaunchKernelGGL(pm_kernel_last_kernel, dim3(blocks_for(mm, f.L)), threads, 0, s, f, n, h, eps * eps, G, c);
+    hipLaunchKernelGGL(pm_kernel_last_kernel, dim3(blocks_for(mm, f.L)), threads, 0, s, f, n, h, eps * eps, G, len, c);
     hipLaunchKernelGGL(pm_kernel_mid_kernel, dim3(batches, nk), threads, 0, s, f, n, c);
     hipLaunchKernelGGL(pm_kernel_first_kernel, dim3(batches, nk), threads, 0, s, f, n, (const double2*)c,
-                       1.0 / (double)M3, ps, sz);
+                       1.0 / (double)M3, 1.0 / len, ps, sz);
   }
   hipLaunchKernelGGL(pm_clear_kernel, dim3(blocks_for(n3, 256)), dim3(256), 0, s, rho, n3);
   if (np > 0)
@@ -1283,7 +1291,7 @@ hipError_t launch_pm_build(const double* xyzm, int64_t np, double eps, const dou
     hipLaunchKernelGGL(pm_product_kernel<false>, dim3(batches, M), threads, 0, s, f, (const double2*)mass, n, n, nk,
                        (const double2*)ps, (const double*)sz, 0.0, 0.0, out);
   hipLaunchKernelGGL(pm_ifft_mid_kernel, dim3(batches, n, 4), threads, 0, s, f, out, nk, n);
-  hipLaunchKernelGGL(pm_ifft_real_kernel, dim3(blocks_for(lines, f.L), 1, 2), threads, 0, s, f, out, M, n, nk, fields);
+  hipLaunchKernelGGL(pm_ifft_real_kernel, dim3(blocks_for(lines, 2 * f.L), 1, 4), threads, 0, s, f, out, M, n, nk, fields);
   const double* values = fields;
   if (periodic) return launch_spline_z<true>(values, fields + 4 * n3, n, h, 4 * lines, s);
   return launch_spline_z<false>(values, fields + 4 * n3, n, h, 4 * lines, s);
