@@ -89,9 +89,6 @@ constexpr int kKahanRounds = 256;        // rounds of plain FP32 sums between co
 constexpr int kGuardRounds = 32;         // the same where the test runs
 constexpr float kNearRatio2 = 1048576.f;   // (1024)^2
 constexpr float kNearFloor2 = 1e-8f;     // (1e-4 Mpc)^2
-// LDS bytes per wavefront of the FP32 path: its tile, and at least what its
-// share of the moment reduction needs ([20][64] floats, [4][64] doubles, and
-// the group's [20][7] double totals).
 // LDS of the FP32 path, per workgroup: WPR tiles (one per wavefront index q of
 // the ray groups; the NG groups of a workgroup share them), each TP float4
 // (x, y in the set's frame, z relative to the stage, m, or z^2 + eps^2 for a
@@ -99,11 +96,11 @@ constexpr float kNearFloor2 = 1e-8f;     // (1e-4 Mpc)^2
 // (the rounding residuals of x and y).  After the last tile the same bytes hold
 // the moment reduction: per wavefront [20][64] floats and [4][64] doubles.
 // Beside them, kept from one field evaluation to the next: per group [20][7] double
-// totals, per wavefront its list of near particles (float4, then float2) and its length.
+// totals, per wavefront its list of near particles (float4, then float2) and where it stands (NearList::Mark).
 constexpr int kRedBytes = kMom * 64 * 4 + 4 * 64 * 8;
 static_assert(kRedBytes % 16 == 0, "reduction areas stay 16-byte aligned");
 constexpr int kNearList = 62;            // particles: a halo's core holds some near ones per wavefront and stage
-constexpr int kNearBytes = kNearList * 24;
+constexpr int kNearBytes = kNearList * 24 + 16;
 static_assert(kNearBytes % 16 == 0 && kMom * kSeg * 8 % 16 == 0, "kept areas stay 16-byte aligned");
 template <int NW, int WPR, int TP>
 struct Lds32 {
@@ -212,22 +209,29 @@ __device__ __forceinline__ void near_direct(const float4 p, const float2 lo, flo
   d[3] += w * rz;
 }
 
-// The near particles that a wavefront met, in the order of the sum; lost: there were more than
-// fit.  (The list is filled in the moment loops, its terms are summed after them: no FP64 term lives
-// in those loops' registers.)
+// The near particles that a wavefront met, in the order of the sum.  (The list is filled in the moment loops, its
+// terms are summed after them: no FP64 term lives in those loops' registers.)  Those that do not fit are found
+// again in the tiles, from the round of nine where the list was full to the last tile that held one.
 struct NearList {
+  struct Mark {           // kept in LDS with the list
+    int n;                // particles listed
+    int first, round;     // tile (of this wavefront's) and its round of the first that did not fit; first < 0: all did
+    int last;             // tile of the last one
+  };
   float4* p;
   float2* lo;
-  int n;
-  bool lost;
+  Mark* mark;
+  Mark at;
+  bool missed;            // in the present tile
 };
+static_assert(sizeof(NearList::Mark) == 16, "kNearBytes holds it");
 
 // The listed particles' terms at the lane's ray, each where its pair is near for the lane's bundle.
 template <bool EQUAL>
 __device__ __forceinline__ void near_terms(const NearList& list, float ex, float ey, float e2, float thr, double dx,
                                            double dy, double dz, double (&d)[4]) {
 #pragma unroll 1
-  for (int j = 0; j < list.n; ++j) {
+  for (int j = 0; j < list.at.n; ++j) {
     const float4 p = list.p[j];
     const float2 lo = list.lo[j];
     if (near_pair<EQUAL>(p, lo, ex, ey, e2, thr)) near_direct<EQUAL>(p, lo, ex, ey, e2, dx, dy, dz, d);
@@ -241,55 +245,59 @@ __device__ __forceinline__ void kahan_add(float& s, float& c, float v) {
   s = t;
 }
 
+// Round i's particles near for some bundle, of the nine (m: the lanes with one; lane 63 repeats another's pair).
+__device__ __forceinline__ unsigned near_slots(unsigned long long m) {
+  unsigned slots = 0;
+#pragma unroll
+  for (int b = 0; b < kSeg; ++b) slots |= (unsigned)(m >> (9 * b)) & 0x1ffu;
+  return slots;
+}
+
 // Round i's near particles (m: the lanes with one) join the list.
 __device__ __forceinline__ void near_found(unsigned long long m, const float4* tile, const float2* tlo, int i, int lane,
                                            NearList& list) {
-  unsigned slots = 0;   // of the round's nine particles (lane 63 repeats another's pair)
-#pragma unroll
-  for (int b = 0; b < kSeg; ++b) slots |= (unsigned)(m >> (9 * b)) & 0x1ffu;
-  if (list.n > kNearList - 9) {
-    list.lost = true;
+  if (list.at.n > kNearList - 9) {
+    if (list.at.first < 0 && !list.missed) list.at.round = i;
+    list.missed = true;
     return;
   }
+  const unsigned slots = near_slots(m);
   if (lane < 9 && (slots >> lane & 1)) {
-    const int at = list.n + __popc(slots & ((1u << lane) - 1u));
+    const int at = list.at.n + __popc(slots & ((1u << lane) - 1u));
     list.p[at] = tile[9 * i + lane];
     list.lo[at] = tlo[9 * i + lane];
   }
-  list.n += __popc(slots);
+  list.at.n += __popc(slots);
 }
 
-// This wavefront's share of a tile: plain FP32 moment sums; a guarded sum leaves near pairs
-// out, and the round's ballot shows its particles that are near for some bundle, which join the list.
-// (Summing each tile twice, with the near pairs in and then out, and testing every particle
-// of it for the near ones made the cost of one near pair that of two more passes over its tile: 2 steps
-// of 258048 rays through the core of a 1e5-particle halo took 74 ms with tiles of 2304, 18 with 288; now 17.5 and 22.)
+// This wavefront's share of a tile, its rounds from `from` to `to`: plain FP32 moment sums; a guarded sum leaves near
+// pairs out and then, where it met some, looks at its rounds again for the particles that are near for some bundle, which
+// join the list.  (Looking while summing, every four rounds, kept the loads of the next rounds behind the branch: the halo
+// band 13.8 ms, 13.2 so.  Summing each tile twice, with the near pairs in and then out, made the cost of one near
+// pair that of a pass over its tile.)
 template <bool EQUAL, bool GUARD>
-__device__ __forceinline__ void tile_moments(const float4* tile, const float2* tlo, int rounds, int l, int lane, float ex,
+__device__ __forceinline__ void tile_moments(const float4* tile, const float2* tlo, int from, int to, int l, int lane, float ex,
                                              float ey, float e2, float thr, float (&a)[kMom], NearList& list) {
   if constexpr (!GUARD) {
 #pragma unroll 8
-    for (int i = 0; i < rounds; ++i) moment_terms<EQUAL, false>(tile[9 * i + l], tlo[9 * i + l], ex, ey, e2, thr, a);
+    for (int i = from; i < to; ++i) moment_terms<EQUAL, false>(tile[9 * i + l], tlo[9 * i + l], ex, ey, e2, thr, a);
   } else {
-    constexpr int U = 4;   // rounds per look at their near lanes
-    int i = 0;
-    for (; i + U <= rounds; i += U) {
-      unsigned long long near[U], any = 0;
+    unsigned long long some = 0;
+    constexpr int U = 8;
+    int i = from;
+    for (; i + U <= to; i += U) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        near[u] = __ballot(moment_terms<EQUAL, true>(tile[9 * (i + u) + l], tlo[9 * (i + u) + l], ex, ey, e2, thr, a));
-        any |= near[u];
-      }
-      if (any) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (near[u]) near_found(near[u], tile, tlo, i + u, lane, list);
-      }
+      for (int u = 0; u < U; ++u)
+        some |= __ballot(moment_terms<EQUAL, true>(tile[9 * (i + u) + l], tlo[9 * (i + u) + l], ex, ey, e2, thr, a));
     }
-    for (; i < rounds; ++i) {
-      const unsigned long long near =
-          __ballot(moment_terms<EQUAL, true>(tile[9 * i + l], tlo[9 * i + l], ex, ey, e2, thr, a));
-      if (near) near_found(near, tile, tlo, i, lane, list);
+#pragma unroll 1
+    for (; i < to; ++i) some |= __ballot(moment_terms<EQUAL, true>(tile[9 * i + l], tlo[9 * i + l], ex, ey, e2, thr, a));
+    if (some) {
+#pragma unroll 1
+      for (i = from; i < to; ++i) {
+        const unsigned long long near = __ballot(near_pair<EQUAL>(tile[9 * i + l], tlo[9 * i + l], ex, ey, e2, thr));
+        if (near) near_found(near, tile, tlo, i, lane, list);
+      }
     }
   }
 }
@@ -375,17 +383,22 @@ __device__ __forceinline__ void moment_tiles(const DevSet& s, float4* tile, int 
         // (sums with near pairs hold larger terms: 256 plain rounds moved mu of the halo's bundles by 2.5e-7
         // against 1.0e-7, for 6% of time)
         for (int r0 = 0; r0 < rounds; r0 += kGuardRounds) {
-          const int cnt = rounds - r0 < kGuardRounds ? rounds - r0 : kGuardRounds;
-          tile_moments<EQUAL, true>(tile + 9 * r0, tlo + 9 * r0, cnt, l, lane, ex, ey, e2, thr, acc, list);
+          const int to = rounds - r0 < kGuardRounds ? rounds : r0 + kGuardRounds;
+          tile_moments<EQUAL, true>(tile, tlo, r0, to, l, lane, ex, ey, e2, thr, acc, list);
 #pragma unroll
           for (int k = 0; k < kMom; ++k) {
             kahan_add(ks[k], kc[k], acc[k]);
             acc[k] = 0.f;
           }
         }
+        if (list.missed) {
+          if (list.at.first < 0) list.at.first = (int)it;
+          list.at.last = (int)it;
+          list.missed = false;
+        }
       } else {
         // plain sums over kKahanRounds rounds of the nine lanes, then one compensated add
-        tile_moments<EQUAL, false>(tile, tlo, rounds, l, lane, ex, ey, e2, thr, acc, list);
+        tile_moments<EQUAL, false>(tile, tlo, 0, rounds, l, lane, ex, ey, e2, thr, acc, list);
         if (++since >= kTilesPerKahan || ch + WPR >= n_tiles) {
 #pragma unroll
           for (int k = 0; k < kMom; ++k) {
@@ -400,26 +413,46 @@ __device__ __forceinline__ void moment_tiles(const DevSet& s, float4* tile, int 
   }
 }
 
-// The direct terms of every near pair, tile by tile: for a workgroup one of whose wavefronts met more
-// of them than its list holds.
+// The direct terms of the near pairs that did not fit a list, from tile round it0 to it1, where some
+// wavefront of the workgroup has them; each looks at its own (mark).  The nine lanes of a bundle test nine
+// particles at a time, as in the moment loop.  Bound: the tiles' staging and the test, about a third of a moment sum.
+// (50000 particles, 129024 rays, 6 steps, lists full at every plane: 19.0 ms, 9.5 without near pairs.  A walk of every
+// tile by every lane, one particle after the other, with the plane summed at both of its visits: 116.  A sum at every stage
+// that walked the tiles of near pairs like that: 118.)
 template <int TP, int WPR, int NG, bool EQUAL>
 __device__ __forceinline__ void near_tiles(const DevSet& s, float4* tile, int q, int g, int lane, float ex, float ey, float thr,
-                                           double dx, double dy, double dz, double zrel, double (&dir)[4]) {
-  const int64_t n_tiles = (s.n + TP - 1) / TP, n_rounds = (n_tiles + WPR - 1) / WPR;
+                                           double dx, double dy, double dz, double zrel, int it0, int it1,
+                                           const NearList::Mark& mark, double (&dir)[4]) {
+  const int64_t n_tiles = (s.n + TP - 1) / TP;
   const float e2 = s.eps2f;
+  const int l = lane < kLanes ? lane % 9 : 0;
   float2* tlo = reinterpret_cast<float2*>(tile + TP);
   const float zr_hi = uniform((float)zrel), zr_lo = uniform((float)(zrel - (double)(float)zrel));
-  for (int64_t it = 0; it < n_rounds; ++it) {
-    const int64_t ch = q + it * WPR, base = ch * TP;
+  for (int it = it0; it <= it1; ++it) {
+    const int64_t ch = q + (int64_t)it * WPR, base = ch * TP;
     if (ch < n_tiles) stage_tile<TP, NG, EQUAL>(s, base, tile, tlo, g, lane, e2, zr_hi, zr_lo);
     __syncthreads();
-    if (ch < n_tiles) {
-      const int cnt = s.n - base < TP ? (int)(s.n - base) : TP;
+    if (ch < n_tiles && mark.first >= 0 && it >= mark.first && it <= mark.last) {
+      const int rounds = s.n - base < TP ? (int)((s.n - base + 8) / 9) : TP / 9;
+      constexpr int U = 4;   // rounds per look at their near lanes
+      for (int i = it == mark.first ? mark.round : 0; i < rounds; i += U) {
+        unsigned long long near[U], any = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int j = 9 * (i + u < rounds ? i + u : rounds - 1) + l;
+          near[u] = __ballot(i + u < rounds && near_pair<EQUAL>(tile[j], tlo[j], ex, ey, e2, thr));
+          any |= near[u];
+        }
+        if (any == 0) continue;
+        // (a lane walks its own bundle's)
 #pragma unroll 1
-      for (int j = 0; j < cnt; ++j) {
-        const float4 p = tile[j];
-        const float2 lo = tlo[j];
-        if (near_pair<EQUAL>(p, lo, ex, ey, e2, thr)) near_direct<EQUAL>(p, lo, ex, ey, e2, dx, dy, dz, dir);
+        for (int u = 0; u < U; ++u) {
+          const unsigned long long m = u == 0 ? near[0] : (u == 1 ? near[1] : (u == 2 ? near[2] : near[3]));
+          for (unsigned slots = (unsigned)(m >> (9 * lane_segment(lane))) & 0x1ffu; slots != 0; slots &= slots - 1) {
+            const int j = 9 * (i + u) + __ffs(slots) - 1;
+            near_direct<EQUAL>(tile[j], tlo[j], ex, ey, e2, dx, dy, dz, dir);
+          }
+        }
       }
     }
     __syncthreads();
@@ -464,9 +497,8 @@ struct PlaneCache {
   double z;
   float ex, ey, thr;
   int set = -1;       // index of the set, -1: nothing kept
-  int near_n = 0;     // near particles of this wavefront's list
-  bool near_lost = false;  // it does not hold all of them
-  bool near_any = false;   // of any wavefront of the workgroup
+  bool near_any = false;   // some wavefront of the workgroup has near pairs,
+  bool near_lost = false;  // and more than its list holds
 };
 enum { VISIT_FIRST = 0, VISIT_MIDDLE = 1, VISIT_END = 2 };
 
@@ -534,57 +566,27 @@ struct FieldEval32 {
     float thr = fmaxf(__int_as_float((__float_as_int(thr_min) + 0x3ffff) & ~0x3ffff), s.eps2f);
     double* tot = reinterpret_cast<double*>(reinterpret_cast<char*>(lds) + L::kTotAt) + g * kMom * kSeg;   // [20][7]
     char* near_at = reinterpret_cast<char*>(lds) + L::kNearAt + (g * WPR + q) * kNearBytes;
-    NearList list{reinterpret_cast<float4*>(near_at), reinterpret_cast<float2*>(near_at + kNearList * 16), 0, false};
+    NearList list{reinterpret_cast<float4*>(near_at), reinterpret_cast<float2*>(near_at + kNearList * 16),
+                  reinterpret_cast<NearList::Mark*>(near_at + kNearList * 24), {0, -1, 0, -1}, false};
     const bool equal = s.equal_mass && *s.equal_mass;
-    double dir[4] = {0.0, 0.0, 0.0, 0.0};
     char* area = reinterpret_cast<char*>(lds) + g * WPR * kRedBytes;
     float* red = reinterpret_cast<float*>(area);                                   // [WPR][20][64]
     double* dred = reinterpret_cast<double*>(area + WPR * kMom * 64 * 4);          // [WPR][4][64]
-    bool again = false, near_any = false;
+    bool again = false;
     if (LEVEL && visit != VISIT_FIRST) {
       const bool same = visit == VISIT_MIDDLE
                             ? thr_min <= kept.thr
                             : (__float_as_int(ex) == __float_as_int(kept.ex) && __float_as_int(ey) == __float_as_int(kept.ey) &&
                                __float_as_int(thr) == __float_as_int(kept.thr));
-      again = __syncthreads_and(same && !kept.near_lost);
+      again = __syncthreads_and(same);
     }
     if (again) {
       thr = kept.thr;
-      near_any = kept.near_any;
-      if (near_any) {
-        list.n = kept.near_n;
-        if (equal) near_terms<true>(list, ex, ey, s.eps2f, thr, dx, dy, dz, dir);
-        else near_terms<false>(list, ex, ey, s.eps2f, thr, dx, dy, dz, dir);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) dred[(q * 4 + k) * 64 + lane] = dir[k];
-        __syncthreads();
-      }
     } else {
       sum_set(s, equal, lds, g, q, lane, ex, ey, thr, zwg, list);
-      // the near pairs' direct terms of the lane's own ray
-      near_any = __syncthreads_or(list.n > 0);
-      if (near_any) {
-        list.lost = __syncthreads_or(list.lost);
-        if (list.lost) {
-          // (the moments' sums wait in red, which the tiles would overwrite)
-          float own[kMom];
-#pragma unroll
-          for (int k = 0; k < kMom; ++k) own[k] = red[(q * kMom + k) * 64 + lane];
-          __syncthreads();
-          float4* tile = lds + q * L::kTileElems;
-          if (equal) near_tiles<TP, WPR, NG, true>(s, tile, q, g, lane, ex, ey, thr, dx, dy, dz, zwg, dir);
-          else near_tiles<TP, WPR, NG, false>(s, tile, q, g, lane, ex, ey, thr, dx, dy, dz, zwg, dir);
-#pragma unroll
-          for (int k = 0; k < kMom; ++k) red[(q * kMom + k) * 64 + lane] = own[k];
-        } else if (equal) {
-          near_terms<true>(list, ex, ey, s.eps2f, thr, dx, dy, dz, dir);
-        } else {
-          near_terms<false>(list, ex, ey, s.eps2f, thr, dx, dy, dz, dir);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) dred[(q * 4 + k) * 64 + lane] = dir[k];
-        __syncthreads();
-      }
+      if (lane == 0) *list.mark = list.at;
+      kept.near_any = __syncthreads_or(list.at.n > 0);
+      kept.near_lost = kept.near_any && __syncthreads_or(list.at.first >= 0);
       // ---- reduction over the nine lanes of each bundle and the group's wavefronts
       for (int t = q * 64 + lane; t < kMom * kSeg; t += WPR * 64) {
         const int k = t / kSeg, b = t - k * kSeg;
@@ -601,15 +603,40 @@ struct FieldEval32 {
       kept.ey = ey;
       kept.thr = thr;
       kept.set = set_id;
-      kept.near_n = list.n;
-      kept.near_lost = list.lost;
-      kept.near_any = near_any;
+    }
+    // the near pairs' direct terms of the lane's own ray, in the order of the sum
+    if (kept.near_any) {
+      double dir[4] = {0.0, 0.0, 0.0, 0.0};
+      const NearList::Mark mark = *list.mark;   // (the same for the wavefront)
+      list.at = NearList::Mark{__builtin_amdgcn_readfirstlane(mark.n), __builtin_amdgcn_readfirstlane(mark.first),
+                               __builtin_amdgcn_readfirstlane(mark.round), __builtin_amdgcn_readfirstlane(mark.last)};
+      if (equal) near_terms<true>(list, ex, ey, s.eps2f, thr, dx, dy, dz, dir);
+      else near_terms<false>(list, ex, ey, s.eps2f, thr, dx, dy, dz, dir);
+      if (kept.near_lost) {
+        int it0 = list.at.first, it1 = list.at.last;
+        const char* marks = reinterpret_cast<const char*>(lds) + L::kNearAt + kNearList * 24;
+        for (int w = 0; w < NW; ++w) {
+          const NearList::Mark m = *reinterpret_cast<const NearList::Mark*>(marks + w * kNearBytes);
+          if (m.first >= 0) {
+            it0 = it0 < 0 || m.first < it0 ? m.first : it0;
+            it1 = m.last > it1 ? m.last : it1;
+          }
+        }
+        it0 = __builtin_amdgcn_readfirstlane(it0);
+        it1 = __builtin_amdgcn_readfirstlane(it1);
+        float4* tile = lds + q * L::kTileElems;
+        if (equal) near_tiles<TP, WPR, NG, true>(s, tile, q, g, lane, ex, ey, thr, dx, dy, dz, zwg, it0, it1, list.at, dir);
+        else near_tiles<TP, WPR, NG, false>(s, tile, q, g, lane, ex, ey, thr, dx, dy, dz, zwg, it0, it1, list.at, dir);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) dred[(q * 4 + k) * 64 + lane] = dir[k];
+      __syncthreads();
     }
     double M[kMom];
 #pragma unroll
     for (int k = 0; k < kMom; ++k) M[k] = tot[k * kSeg + seg];
     double D0 = 0.0, D1 = 0.0, D2 = 0.0, D3 = 0.0;
-    if (near_any) {
+    if (kept.near_any) {
 #pragma unroll
       for (int w = 0; w < WPR; ++w) {
         D0 += dred[(w * 4 + 0) * 64 + lane];
