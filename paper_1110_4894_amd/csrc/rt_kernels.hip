@@ -480,7 +480,7 @@ __device__ __forceinline__ void small_set_fp64(const DevCosmo& c, const DevSet& 
 // the list.  That halves the pair terms; the error stays that of the expansion, whose
 // nearness test the new offsets have to pass.
 //   * middle: the second visit keeps the first one's expansion points and runs if every
-//     bundle's threshold still covers its offsets;
+//     bundle's threshold still covers its offsets (otherwise it sums anew, about its own points);
 //   * end: it runs only if its own expansion points and thresholds equal the kept ones
 //     bit by bit, so that it gives what a sum from the start would give, and a trace resumed
 //     at that node gives the same rays as one that went through.  Expansion points are
@@ -533,11 +533,6 @@ struct FieldEval32 {
       ex = (float)xa;
       ey = (float)ya;
     }
-    if (visit == VISIT_MIDDLE) {
-      ex = kept.ex;
-      ey = kept.ey;
-    }
-    const double dx = X - (double)ex, dy = Yv - (double)ey;
     double zwg = Zl, dz = 0.0;
     bool level = true;
     if constexpr (!LEVEL) {
@@ -552,15 +547,28 @@ struct FieldEval32 {
     }
     // largest offset in the bundle -> nearness threshold on s
     const int l = lane < kLanes ? lane % 9 : 0;
-    const float fx = (float)dx, fy = (float)dy;
-    float m2 = lane < kLanes ? fmaf(fx, fx, fy * fy) : 0.f;
+    double dx, dy;
+    float thr_min;
+    auto offsets = [&](float px, float py) {
+      dx = X - (double)px;
+      dy = Yv - (double)py;
+      const float fx = (float)dx, fy = (float)dy;
+      float m2 = lane < kLanes ? fmaf(fx, fx, fy * fy) : 0.f;
 #pragma unroll
-    for (int off = 1; off < 9; off <<= 1) {
-      const float o = __shfl(m2, (l + off < 9) ? lane + off : lane);
-      m2 = fmaxf(m2, o);
+      for (int off = 1; off < 9; off <<= 1) {
+        const float o = __shfl(m2, (l + off < 9) ? lane + off : lane);
+        m2 = fmaxf(m2, o);
+      }
+      m2 = __shfl(m2, anchor);
+      thr_min = level ? fmaxf(kNearRatio2 * m2, kNearFloor2) : __builtin_inff();
+    };
+    bool again = false;
+    if (LEVEL && visit == VISIT_MIDDLE) {
+      offsets(kept.ex, kept.ey);
+      again = __syncthreads_and(thr_min <= kept.thr);
     }
-    m2 = __shfl(m2, anchor);
-    const float thr_min = level ? fmaxf(kNearRatio2 * m2, kNearFloor2) : __builtin_inff();
+    // (points that the rays have left are no place to expand about: they would raise the threshold)
+    if (!again) offsets(ex, ey);
     // rounded up to 5 bits of mantissa (a threshold that large that this overflows is infinite), and at least
     // eps^2, below which no pair lies and all thresholds are one
     float thr = fmaxf(__int_as_float((__float_as_int(thr_min) + 0x3ffff) & ~0x3ffff), s.eps2f);
@@ -572,15 +580,14 @@ struct FieldEval32 {
     char* area = reinterpret_cast<char*>(lds) + g * WPR * kRedBytes;
     float* red = reinterpret_cast<float*>(area);                                   // [WPR][20][64]
     double* dred = reinterpret_cast<double*>(area + WPR * kMom * 64 * 4);          // [WPR][4][64]
-    bool again = false;
-    if (LEVEL && visit != VISIT_FIRST) {
-      const bool same = visit == VISIT_MIDDLE
-                            ? thr_min <= kept.thr
-                            : (__float_as_int(ex) == __float_as_int(kept.ex) && __float_as_int(ey) == __float_as_int(kept.ey) &&
-                               __float_as_int(thr) == __float_as_int(kept.thr));
+    if (LEVEL && visit == VISIT_END) {
+      const bool same = __float_as_int(ex) == __float_as_int(kept.ex) && __float_as_int(ey) == __float_as_int(kept.ey) &&
+                        __float_as_int(thr) == __float_as_int(kept.thr);
       again = __syncthreads_and(same);
     }
     if (again) {
+      ex = kept.ex;
+      ey = kept.ey;
       thr = kept.thr;
     } else {
       sum_set(s, equal, lds, g, q, lane, ex, ey, thr, zwg, list);

@@ -111,3 +111,17 @@ def test_full_lists_cost_a_second_look_at_their_tiles():
     print("no near pairs %.2f ms, full lists %.2f ms" % (free, full))
     assert full <= 3.0 * free
 
+
+def test_rays_that_leave_the_expansion_points():
+    """A heavy particle beside the filament moves the rays by hundreds of radii between the two visits of a middle
+    plane: the second sum is about their own points, with no more near pairs than the first, and costs what a sum at every
+    stage does, at most twice the launch whose planes are kept (half as much again is allowed; about the points that the
+    rays had left it was more than four times)."""
+    rt.rt_force_plan(FP32K, 0)
+    xyz, m = _filament(50000, "random")
+    kept = Case(xyz, m, 14336, 1e-6, 0.05, 5).ms()
+    xyz, m = _filament(50000, "random", heavy=4e16)
+    moved = Case(xyz, m, 14336, 1e-6, 0.0005, 5).ms()
+    rt.rt_force_plan(FP32K, -1)
+    print("planes kept %.2f ms, rays moved %.2f ms" % (kept, moved))
+    assert moved <= 3.0 * kept
