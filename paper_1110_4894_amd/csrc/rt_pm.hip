@@ -770,6 +770,139 @@ __device__ __forceinline__ void pm_field(const PmGrid& g, const double* __restri
   gz = out[3];
 }
 
+// The same with the splines solved in place, for windows of six and eight nodes a side: their weights and
+// loads in pairs take up to four times as long there (10^6 points of a 128^3 grid in cell order, six a side 1.5 against
+// 3.2 ms, eight 1.9 against 7.3; in random order 5.0 against 6.3 and 8.5 against 12.0), where those of two and four a side
+// are the faster (0.39 against 0.32, 0.89 against 0.67).
+__device__ __forceinline__ double spline_eval(double yk, double yk1, double y2k, double y2k1, double A, double h) {
+  const double B = 1.0 - A;
+  return A * yk + B * yk1 + ((A * A * A - A) * y2k + (B * B * B - B) * y2k1) * (h * h) / 6.0;
+}
+
+// Natural spline through m = 2 NI values at unit-spaced nodes node0 + a (spacing h),
+// evaluated at u (in node units).
+template <int NI>
+__device__ __forceinline__ double local_spline(const double (&v)[2 * NI], int node0, double u, double h) {
+  constexpr int m = 2 * NI;
+  double y2[m];
+  y2[0] = 0.0;
+  y2[m - 1] = 0.0;
+  if constexpr (m >= 3) {
+    const double s = 6.0 / (h * h);
+    double cp[m];
+    double c = 0.0, d = 0.0;
+#pragma unroll
+    for (int k = 1; k < m - 1; ++k) {
+      c = 1.0 / (4.0 - (k > 1 ? c : 0.0));
+      cp[k] = c;
+      d = (s * (v[k + 1] - 2.0 * v[k] + v[k - 1]) - (k > 1 ? d : 0.0)) * c;
+      y2[k] = d;
+    }
+#pragma unroll
+    for (int k = m - 3; k >= 1; --k) y2[k] = y2[k] - cp[k] * y2[k + 1];
+  }
+  int kl = (int)floor(u) - node0;
+  kl = kl < 0 ? 0 : (kl > m - 2 ? m - 2 : kl);
+  const double A = (double)(node0 + kl + 1) - u;
+  double yk = v[0], yk1 = v[1], s2k = y2[0], s2k1 = y2[1];
+#pragma unroll
+  for (int a = 1; a < m - 1; ++a)
+    if (a == kl) {
+      yk = v[a];
+      yk1 = v[a + 1];
+      s2k = y2[a];
+      s2k1 = y2[a + 1];
+    }
+  return spline_eval(yk, yk1, s2k, s2k1, A, h);
+}
+
+__device__ __forceinline__ int wrap(int i, int n) { return ((i % n) + n) % n; }
+
+// App. B on a periodic grid: the point is brought into the box (fmod, then + n
+// for negative values), the x^3 segment and the x^1, x^2 windows are taken
+// modulo n; the local splines see the unwrapped window nodes.
+template <int NI>
+__device__ __forceinline__ void pm_splines_periodic(const PmGrid& g, const double* __restrict__ fields, double x, double y, double z,
+                                  double& phi, double& gx, double& gy, double& gz) {
+  const int n = g.n;
+  const double dn = (double)n;
+  double ux = fmod((x - g.ox) / g.h, dn), uy = fmod((y - g.oy) / g.h, dn), uz = fmod((z - g.oz) / g.h, dn);
+  phi = gx = gy = gz = 0.0;
+  if (!(isfinite(ux) && isfinite(uy) && isfinite(uz))) return;
+  if (ux < 0.0) ux += dn;
+  if (uy < 0.0) uy += dn;
+  if (uz < 0.0) uz += dn;
+  const int fx = (int)floor(ux), fy = (int)floor(uy), fz = (int)floor(uz);
+  const int wx = fx - NI + 1, wy = fy - NI + 1;
+  const int kz0 = wrap(fz, n), kz1 = wrap(fz + 1, n);
+  const double Az = (double)(fz + 1) - uz;
+  const int64_t n3 = (int64_t)n * n * n;
+  double out[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double* F = fields + q * n3;
+    const double* F2 = fields + (q + 4) * n3;
+    double w[2 * NI];
+#pragma unroll
+    for (int b = 0; b < 2 * NI; ++b) {
+      const int j = wrap(wy + b, n);
+      double v[2 * NI];
+#pragma unroll
+      for (int a = 0; a < 2 * NI; ++a) {
+        const int64_t row = ((int64_t)wrap(wx + a, n) * n + j) * n;
+        v[a] = spline_eval(F[row + kz0], F[row + kz1], F2[row + kz0], F2[row + kz1], Az, g.h);
+      }
+      w[b] = local_spline<NI>(v, wx, ux, g.h);
+    }
+    out[q] = local_spline<NI>(w, wy, uy, g.h);
+  }
+  phi = out[0];
+  gx = out[1];
+  gy = out[2];
+  gz = out[3];
+}
+
+// The four grid quantities at (x, y, z): phi and its gradient.
+template <int NI>
+__device__ __forceinline__ void pm_splines(const PmGrid& g, const double* __restrict__ fields, double x, double y, double z, double& phi,
+                         double& gx, double& gy, double& gz) {
+  if (g.periodic) {
+    pm_splines_periodic<NI>(g, fields, x, y, z, phi, gx, gy, gz);
+    return;
+  }
+  const int n = g.n;
+  const double ux = (x - g.ox) / g.h, uy = (y - g.oy) / g.h, uz = (z - g.oz) / g.h;
+  phi = gx = gy = gz = 0.0;
+  if (!(ux >= 0.0 && uy >= 0.0 && uz >= 0.0 && ux <= n - 1 && uy <= n - 1 && uz <= n - 1)) return;
+  const int wx = window_start(ux, n, NI), wy = window_start(uy, n, NI);
+  int kz = (int)floor(uz);
+  kz = kz > n - 2 ? n - 2 : kz;
+  const double Az = (double)(kz + 1) - uz;
+  const int64_t n3 = (int64_t)n * n * n;
+  double out[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double* F = fields + q * n3;
+    const double* F2 = fields + (q + 4) * n3;
+    double w[2 * NI];
+#pragma unroll
+    for (int b = 0; b < 2 * NI; ++b) {
+      double v[2 * NI];
+#pragma unroll
+      for (int a = 0; a < 2 * NI; ++a) {
+        const int64_t at = ((int64_t)(wx + a) * n + (wy + b)) * n + kz;
+        v[a] = spline_eval(F[at], F[at + 1], F2[at], F2[at + 1], Az, g.h);
+      }
+      w[b] = local_spline<NI>(v, wx, ux, g.h);
+    }
+    out[q] = local_spline<NI>(w, wy, uy, g.h);
+  }
+  phi = out[0];
+  gx = out[1];
+  gy = out[2];
+  gz = out[3];
+}
+
 // The rays of a wavefront (seven bundles, lane 9 b + k = ray k of bundle b; lane 63 idle).  The
 // nine rays of a bundle lie parsecs apart and cells are kiloparsecs wide, so they nearly always
 // ask for the same window: its nodes (four values each) are fetched once per bundle, a ninth by
@@ -979,7 +1112,8 @@ __global__ __launch_bounds__(256) void pm_eval_kernel(PmGrid g, const double* __
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
   double p, gx, gy, gz;
-  pm_field<NI>(g, fields, pts[i], pts[np + i], pts[2 * np + i], p, gx, gy, gz);
+  if constexpr (NI <= 2) pm_field<NI>(g, fields, pts[i], pts[np + i], pts[2 * np + i], p, gx, gy, gz);
+  else pm_splines<NI>(g, fields, pts[i], pts[np + i], pts[2 * np + i], p, gx, gy, gz);
   phi[i] = p;
   grad[i] = gx;
   grad[np + i] = gy;
