@@ -939,6 +939,7 @@ struct PmWave {
     if (!__any(want)) return;
     PmPoint<NI> p{};
     want = want && p.set(g, x, y, z);
+    if (!__any(want)) return;   // (an isolated grid fills little of a ray's way)
     const int seg = lane < 63 ? lane / 9 : 6, k9 = lane - 9 * seg;
     double* raw = lds + seg * kRaw;
     double* val = lds + 7 * kRaw + seg * kVal;
