@@ -1179,7 +1179,9 @@ rt_status rt_trace_pm(const rt_cosmology* cosmo, double z_source, int32_t n_grid
   const int32_t se = step_end > n_steps ? n_steps : step_end;
   if (n_bundles == 0 || step_begin >= se) return RT_OK;
   std::vector<DevPmGrid> hg(n_grids);
+  double h_min = grids[0].h;
   for (int i = 0; i < n_grids; ++i) {
+    h_min = std::min(h_min, grids[i].h);
     hg[i].n = grids[i].n;
     for (int d = 0; d < 3; ++d) hg[i].origin[d] = grids[i].origin[d];
     hg[i].h = grids[i].h;
@@ -1199,7 +1201,7 @@ rt_status rt_trace_pm(const rt_cosmology* cosmo, double z_source, int32_t n_grid
   RT_HIP(hipMemcpyAsync(d_nodes, z_nodes, sizeof(double) * (n_steps + 1), hipMemcpyHostToDevice, stream));
   RT_HIP(hipMemcpyAsync(d_sg, sg.data(), sizeof(int32_t) * n_steps, hipMemcpyHostToDevice, stream));
   RT_HIP(hipStreamSynchronize(stream));   // the host staging above is pageable and local
-  RT_HIP(launch_pm_trace(make_dev_cosmo(*cosmo), d_grids, d_sg, n_int, d_nodes, step_begin, se, rays,
+  RT_HIP(launch_pm_trace(make_dev_cosmo(*cosmo), d_grids, d_sg, n_int, d_nodes, step_begin, se, h_min, rays,
                          9 * n_bundles, ray_flags, stream));
   RT_HIP(sc.release());
   return RT_OK;

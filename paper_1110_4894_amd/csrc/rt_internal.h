@@ -125,8 +125,8 @@ hipError_t launch_pm_build(const double* xyzm, int64_t np, double eps, const dou
 hipError_t launch_pm_eval(const double origin[3], double h, int n, int periodic, const double* fields, int n_int,
                           int64_t np, const double* pts, double* phi, double* grad, hipStream_t s);
 hipError_t launch_pm_trace(DevCosmo c, const DevPmGrid* grids, const int32_t* step_grid, int n_int,
-                           const double* nodes, int32_t step_begin, int32_t step_end, double* rays, int64_t n_rays,
-                           uint8_t* flags, hipStream_t s);
+                           const double* nodes, int32_t step_begin, int32_t step_end, double h_min, double* rays,
+                           int64_t n_rays, uint8_t* flags, hipStream_t s);   // h_min: smallest node spacing of the grids
 hipError_t launch_pm_trace_lambda(DevCosmo c, const double origin[3], double h, int n, int periodic,
                                   const double* fields, int n_int, double chi_s, double f_rk, int32_t max_steps,
                                   double* rays, int64_t n_rays, uint8_t* flags, int32_t* steps, hipStream_t s);

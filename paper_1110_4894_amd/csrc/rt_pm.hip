@@ -903,6 +903,73 @@ __device__ __forceinline__ void pm_splines(const PmGrid& g, const double* __rest
   gz = out[3];
 }
 
+// A node row's value at the point's x^3: two values and two second derivatives.  (Explicit, so that every way to sum a
+// window gives the same bits.)
+__device__ __forceinline__ double along_z(const double (&c)[4], double f0, double f1, double g0, double g1) {
+  return fma(c[0], f0, fma(c[1], f1, fma(c[2], g0, c[3] * g1)));
+}
+
+// A ray on its own lane: its nodes, loaded by itself, ROWS rows of the window (along x^2, of one quantity after the
+// other: the eight grids lie a power of two apart, so that their lines share the sets of a cache) in flight at a
+// time.  PAIR: the two nodes of the x^3 segment are neighbours, which makes one load of them (false where some lane's
+// segment wraps round a periodic line).  With a branch at every pair for the one that wraps, each load waited for the
+// one before.
+template <int NI, int ROWS, bool PAIR>
+__device__ __forceinline__ void pm_gather(const PmPoint<NI>& p, int n, int periodic, const double* __restrict__ fields,
+                                          double (&out)[4]) {
+  constexpr int m = 2 * NI;
+  static_assert(4 * m % ROWS == 0, "whole batches");
+  const int64_t n3 = (int64_t)n * n * n;
+  const int wrap = periodic ? n - 1 : -1;
+  const int k0 = p.kz & wrap, next = PAIR ? 1 : ((p.kz + 1) & wrap) - k0;
+  // where a row starts: the parts of its two indices (n <= 512: below 2^27)
+  unsigned at_x[m], at_y[m];
+#pragma unroll
+  for (int a = 0; a < m; ++a) {
+    at_x[a] = (unsigned)((p.wx + a) & wrap) * (unsigned)(n * n) + (unsigned)k0;
+    at_y[a] = (unsigned)((p.wy + a) & wrap) * (unsigned)n;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) out[q] = 0.0;
+#pragma unroll
+  for (int r0 = 0; r0 < 4 * m; r0 += ROWS) {
+    double v[ROWS][m][4];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const int q = (r0 + r) / m, a = (r0 + r) % m;
+#pragma unroll
+      for (int b = 0; b < m; ++b) {
+        const double *f = fields + q * n3 + (at_x[a] + at_y[b]), *f2 = f + 4 * n3;
+        v[r][b][0] = f[0];
+        v[r][b][1] = f[next];
+        v[r][b][2] = f2[0];
+        v[r][b][3] = f2[next];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const int q = (r0 + r) / m, a = (r0 + r) % m;
+      double w = 0.0;
+#pragma unroll
+      for (int b = 0; b < m; ++b) w = fma(p.y[b], along_z(p.cz, v[r][b][0], v[r][b][1], v[r][b][2], v[r][b][3]), w);
+      out[q] = fma(p.x[a], w, out[q]);
+    }
+  }
+}
+
+// The same for the lanes with a point of a wavefront all of whose lanes call it.
+template <int NI, int ROWS>
+__device__ __forceinline__ void pm_gather_lanes(bool want, const PmPoint<NI>& p, int n, int periodic,
+                                                const double* __restrict__ fields, double (&out)[4]) {
+  const bool pair = !periodic || (p.kz & (n - 1)) + 1 < n;
+  if (__all(!want || pair)) {
+    if (want) pm_gather<NI, ROWS, true>(p, n, periodic, fields, out);
+  } else if (want) {
+    pm_gather<NI, ROWS, false>(p, n, periodic, fields, out);
+  }
+}
+
 // The rays of a wavefront (seven bundles, lane 9 b + k = ray k of bundle b; lane 63 idle).  The
 // nine rays of a bundle lie parsecs apart and cells are kiloparsecs wide, so they nearly always
 // ask for the same window: its nodes (four values each) are fetched once per bundle, a ninth by
@@ -1031,7 +1098,7 @@ struct PmWave {
         for (int r = 0; r < kRounds; ++r) {
           const int t = k9 + 9 * r;
           if (t < kNodes)
-            val[t] = c[0] * raw[4 * t] + c[1] * raw[4 * t + 1] + (c[2] * raw[4 * t + 2] + c[3] * raw[4 * t + 3]);
+            val[t] = along_z(c, raw[4 * t], raw[4 * t + 1], raw[4 * t + 2], raw[4 * t + 3]);
         }
       }
       lds_sync();
@@ -1084,7 +1151,7 @@ struct PmWave {
           const double* t = v + C * ((q * m + a) * m + b);
           if constexpr (C == 1) w = fma(p.y[b], t[0], w);
           else if constexpr (C == 2) w = fma(p.y[b], fma(c[1], t[1], t[0]), w);
-          else w = fma(p.y[b], c[0] * t[0] + c[1] * t[1] + (c[2] * t[2] + c[3] * t[3]), w);
+          else w = fma(p.y[b], along_z(c, t[0], t[1], t[2], t[3]), w);
         }
         s = fma(p.x[a], w, s);
       }
@@ -1107,6 +1174,41 @@ struct PmWave {
   }
 };
 
+// The rays of a wavefront whose bundles are wider than cells: every ray loads its own nodes.
+template <int NI>
+struct PmLanes {
+  __device__ __forceinline__ void eval(double*, int, bool want, int, const PmGrid& g, const double* fields, double x, double y,
+                                       double z, double& phi, double& gx, double& gy, double& gz) {
+    phi = gx = gy = gz = 0.0;
+    if (!__any(want)) return;
+    PmPoint<NI> p{};
+    double out[4] = {0.0, 0.0, 0.0, 0.0};
+    want = want && p.set(g, x, y, z);
+    pm_gather_lanes<NI, NI == 1 ? 8 : (NI == 2 ? 4 : (NI == 3 ? 2 : 1))>(want, p, g.n, g.periodic, fields, out);
+    phi = out[0];
+    gx = out[1];
+    gy = out[2];
+    gz = out[3];
+  }
+};
+
+// Whether some bundle of the wavefront becomes wide on straight lines to z_end: a ray more than a twentieth of a
+// node spacing h (for windows of two nodes a side, whose loads are few, a thousandth) away from its anchor.  Its rays then ask for different windows at many stages, and a round of
+// fetching for each takes longer than a load of every ray's own nodes: the wavefront takes that way from the start.
+// Both give a ray the same bits in z.  4096 bundles through a periodic 128^3 mesh, four nodes a side, 40 steps in z, rings of a
+// fifteenth, two thirds and seven spacings: shared 2.3, 4.6, 11.2 ms, own nodes 1.6, 2.2, 8.5; of a 150th 1.9 and 2.9.
+template <int NI>
+__device__ __forceinline__ bool wide_bundles(int lane, bool valid, const double* rays, int64_t N, int64_t ri, double z_end,
+                                             double h) {
+  const int anchor = lane < 63 ? lane - lane % 9 : 54;
+  const double x = rays[N + ri], y = rays[2 * N + ri], l = fabs(z_end - rays[3 * N + ri]);
+  const double ik = 1.0 / rays[7 * N + ri], sx = rays[5 * N + ri] * ik, sy = rays[6 * N + ri] * ik;
+  const double dx = fabs(x - __shfl(x, anchor)) + fabs(sx - __shfl(sx, anchor)) * l;
+  const double dy = fabs(y - __shfl(y, anchor)) + fabs(sy - __shfl(sy, anchor)) * l;
+  const double limit = (NI == 1 ? 0.001 : 0.05) * h;
+  return __any(valid && (dx > limit || dy > limit));
+}
+
 template <int NI>
 __global__ __launch_bounds__(256) void pm_eval_kernel(PmGrid g, const double* __restrict__ fields, int64_t np,
                                                       const double* __restrict__ pts, double* phi, double* grad) {
@@ -1127,21 +1229,17 @@ __global__ __launch_bounds__(256) void pm_eval_kernel(PmGrid g, const double* __
 // flags as the direct-sum trace kernel, with the field of step s taken from grid
 // step_grid[s] (none for -1): one isolated grid for a lens, one periodic grid
 // per box replica for a light cone.
-template <int NI>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI == 3 ? 1 : 2, NI == 3 ? 1 : 2))) void pm_trace_kernel(
-    DevCosmo cz, const DevPmGrid* __restrict__ grids, const int32_t* __restrict__ step_grid,
-    const double* __restrict__ nodes, int32_t step_begin, int32_t step_end, double* rays, int64_t N, uint8_t* flags) {
-  __shared__ double lds[PmWave<NI, true>::kDoubles];
+template <int NI, class Mesh>
+__device__ __forceinline__ void pm_trace_rays(Mesh mesh, double* lds, const DevCosmo& cz, const DevPmGrid* __restrict__ grids,
+                                              const int32_t* __restrict__ step_grid, const double* __restrict__ nodes,
+                                              int32_t step_begin, int32_t step_end, double* rays, int64_t N, int64_t ri,
+                                              bool valid, uint8_t* flags) {
   const int lane = threadIdx.x;
-  const int64_t at = (int64_t)blockIdx.x * 63 + lane;
-  const bool valid = lane < 63 && at < N;
-  const int64_t ri = valid ? at : N - 1;
   State Y{rays[ri], rays[N + ri], rays[2 * N + ri], rays[4 * N + ri], rays[5 * N + ri], rays[6 * N + ri],
           rays[7 * N + ri]};
   double zpos = rays[3 * N + ri];
   uint8_t flag = 0;
   bool live = valid;
-  PmWave<NI, true> mesh;
   int cur = -1;
   PmGrid g{0, 0.0, 0.0, 0.0, 1.0, 0, 1.0};
   const double* fields = nullptr;
@@ -1208,6 +1306,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI == 3 ? 1 
   if (flags && flag) flags[ri] |= flag;
 }
 
+template <int NI>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI >= 3 ? 1 : 2, NI >= 3 ? 1 : 2))) void pm_trace_kernel(
+    DevCosmo cz, const DevPmGrid* __restrict__ grids, const int32_t* __restrict__ step_grid,
+    const double* __restrict__ nodes, int32_t step_begin, int32_t step_end, double h_min, double* rays, int64_t N,
+    uint8_t* flags) {
+  __shared__ double lds[PmWave<NI, true>::kDoubles];
+  const int64_t at = (int64_t)blockIdx.x * 63 + threadIdx.x;
+  const bool valid = threadIdx.x < 63 && at < N;
+  const int64_t ri = valid ? at : N - 1;
+  if (wide_bundles<NI>(threadIdx.x, valid, rays, N, ri, nodes[step_end], h_min))
+    pm_trace_rays<NI>(PmLanes<NI>{}, lds, cz, grids, step_grid, nodes, step_begin, step_end, rays, N, ri, valid, flags);
+  else
+    pm_trace_rays<NI>(PmWave<NI, true>{}, lds, cz, grids, step_grid, nodes, step_begin, step_end, rays, N, ri, valid, flags);
+}
+
 // The paper's own integrator (Sec. 3.4, eq. RKstepsize): classical RK4 in the
 // affine parameter with the fixed step f_RK h / kz_0 (h: the Fourier-grid
 // spacing, kz_0: the ray's dz/dlambda at the start), repeated until z reaches
@@ -1270,22 +1383,17 @@ struct SlabGrids {
   }
 };
 
-template <int NI, class Grids>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void pm_trace_lambda_kernel(
-    DevCosmo cz, Grids grids, double h_rk, double chi_s, double f_rk, int32_t max_steps, double* rays, int64_t N,
-    uint8_t* flags, int32_t* steps_out) {
-  __shared__ double lds[PmWave<NI, false>::kDoubles];
+template <int NI, class Grids, class Mesh>
+__device__ __forceinline__ void pm_trace_rays_lambda(Mesh mesh, double* lds, const DevCosmo& cz, const Grids& grids, double h_rk,
+                                                     double chi_s, double f_rk, int32_t max_steps, double* rays, int64_t N,
+                                                     int64_t ri, bool valid, uint8_t* flags, int32_t* steps_out) {
   const int lane = threadIdx.x;
-  const int64_t at = (int64_t)blockIdx.x * 63 + lane;
-  const bool valid = lane < 63 && at < N;
-  const int64_t ri = valid ? at : N - 1;
   State8 Y{rays[ri],         rays[N + ri],     rays[2 * N + ri], rays[3 * N + ri],
            rays[4 * N + ri], rays[5 * N + ri], rays[6 * N + ri], rays[7 * N + ri]};
   const double dl = f_rk * h_rk / Y.kz;
   uint8_t flag = 0;
   bool done = !valid || !(Y.z < chi_s);
   int32_t steps = 0;
-  PmWave<NI, false> mesh;
   int gi = -1;
   PmGrid g{4, 0.0, 0.0, 0.0, 1.0, 0, 1.0};
   const double* fields = nullptr;
@@ -1340,6 +1448,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   rays[7 * N + ri] = Y.kz;
   if (flags && flag) flags[ri] |= flag;
   if (steps_out) steps_out[ri] = steps;
+}
+
+template <int NI, class Grids>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI == 4 ? 1 : 2, NI == 4 ? 1 : 2))) void pm_trace_lambda_kernel(
+    DevCosmo cz, Grids grids, double h_rk, double chi_s, double f_rk, int32_t max_steps, double* rays, int64_t N,
+    uint8_t* flags, int32_t* steps_out) {
+  __shared__ double lds[PmWave<NI, false>::kDoubles];
+  const int64_t at = (int64_t)blockIdx.x * 63 + threadIdx.x;
+  const bool valid = threadIdx.x < 63 && at < N;
+  const int64_t ri = valid ? at : N - 1;
+  if (wide_bundles<NI>(threadIdx.x, valid, rays, N, ri, chi_s, h_rk))
+    pm_trace_rays_lambda<NI>(PmLanes<NI>{}, lds, cz, grids, h_rk, chi_s, f_rk, max_steps, rays, N, ri, valid, flags, steps_out);
+  else
+    pm_trace_rays_lambda<NI>(PmWave<NI, false>{}, lds, cz, grids, h_rk, chi_s, f_rk, max_steps, rays, N, ri, valid, flags,
+                             steps_out);
 }
 
 inline unsigned blocks_for(int64_t count, int threads) { return (unsigned)((count + threads - 1) / threads); }
@@ -1446,11 +1569,11 @@ hipError_t launch_pm_eval(const double origin[3], double h, int n, int periodic,
 }
 
 hipError_t launch_pm_trace(DevCosmo c, const DevPmGrid* grids, const int32_t* step_grid, int n_int,
-                           const double* nodes, int32_t step_begin, int32_t step_end, double* rays, int64_t n_rays,
+                           const double* nodes, int32_t step_begin, int32_t step_end, double h_min, double* rays, int64_t n_rays,
                            uint8_t* flags, hipStream_t s) {
   const dim3 grid(blocks_for(n_rays, 63)), block(64);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, c, grids, step_grid, nodes, step_begin, step_end, rays, n_rays,
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, c, grids, step_grid, nodes, step_begin, step_end, h_min, rays, n_rays,
                        flags);
   };
   switch (n_int) {
