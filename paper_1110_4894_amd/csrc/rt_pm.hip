@@ -929,31 +929,45 @@ __device__ __forceinline__ void pm_gather(const PmPoint<NI>& p, int n, int perio
     at_x[a] = (unsigned)((p.wx + a) & wrap) * (unsigned)(n * n) + (unsigned)k0;
     at_y[a] = (unsigned)((p.wy + a) & wrap) * (unsigned)n;
   }
+  // `count` rows (quantity, index along x^1) from the quantity at `first` on
+  auto rows = [&](const double* first, int count, auto& sum) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) out[q] = 0.0;
+    for (int r0 = 0; r0 < count; r0 += ROWS) {
+      double v[ROWS][m][4];
 #pragma unroll
-  for (int r0 = 0; r0 < 4 * m; r0 += ROWS) {
-    double v[ROWS][m][4];
+      for (int r = 0; r < ROWS; ++r) {
+        const int q = (r0 + r) / m, a = (r0 + r) % m;
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-      const int q = (r0 + r) / m, a = (r0 + r) % m;
+        for (int b = 0; b < m; ++b) {
+          const double *f = first + q * n3 + (at_x[a] + at_y[b]), *f2 = f + 4 * n3;
+          v[r][b][0] = f[0];
+          v[r][b][1] = f[next];
+          v[r][b][2] = f2[0];
+          v[r][b][3] = f2[next];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int b = 0; b < m; ++b) {
-        const double *f = fields + q * n3 + (at_x[a] + at_y[b]), *f2 = f + 4 * n3;
-        v[r][b][0] = f[0];
-        v[r][b][1] = f[next];
-        v[r][b][2] = f2[0];
-        v[r][b][3] = f2[next];
+      for (int r = 0; r < ROWS; ++r) {
+        const int q = (r0 + r) / m, a = (r0 + r) % m;
+        double w = 0.0;
+#pragma unroll
+        for (int b = 0; b < m; ++b) w = fma(p.y[b], along_z(p.cz, v[r][b][0], v[r][b][1], v[r][b][2], v[r][b][3]), w);
+        sum[q] = fma(p.x[a], w, sum[q]);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
+  };
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-      const int q = (r0 + r) / m, a = (r0 + r) % m;
-      double w = 0.0;
+  for (int q = 0; q < 4; ++q) out[q] = 0.0;
+  if constexpr (NI < 4) {
+    rows(fields, 4 * m, out);
+  } else {   // (unrolled, the quantities' addresses are all kept, and spilled)
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      double s[1] = {0.0};
+      rows(fields + q * n3, m, s);
 #pragma unroll
-      for (int b = 0; b < m; ++b) w = fma(p.y[b], along_z(p.cz, v[r][b][0], v[r][b][1], v[r][b][2], v[r][b][3]), w);
-      out[q] = fma(p.x[a], w, out[q]);
+      for (int t = 0; t < 4; ++t) out[t] = q == t ? s[0] : out[t];
     }
   }
 }
@@ -1184,7 +1198,7 @@ struct PmLanes {
     PmPoint<NI> p{};
     double out[4] = {0.0, 0.0, 0.0, 0.0};
     want = want && p.set(g, x, y, z);
-    pm_gather_lanes<NI, NI == 1 ? 8 : (NI == 2 ? 4 : (NI == 3 ? 2 : 1))>(want, p, g.n, g.periodic, fields, out);
+    pm_gather_lanes<NI, NI == 1 ? 8 : (NI == 4 ? 1 : 2)>(want, p, g.n, g.periodic, fields, out);
     phi = out[0];
     gx = out[1];
     gy = out[2];
@@ -1307,7 +1321,7 @@ __device__ __forceinline__ void pm_trace_rays(Mesh mesh, double* lds, const DevC
 }
 
 template <int NI>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI >= 3 ? 1 : 2, NI >= 3 ? 1 : 2))) void pm_trace_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI == 3 ? 1 : 2, NI == 3 ? 1 : 2))) void pm_trace_kernel(
     DevCosmo cz, const DevPmGrid* __restrict__ grids, const int32_t* __restrict__ step_grid,
     const double* __restrict__ nodes, int32_t step_begin, int32_t step_end, double h_min, double* rays, int64_t N,
     uint8_t* flags) {
@@ -1451,7 +1465,7 @@ __device__ __forceinline__ void pm_trace_rays_lambda(Mesh mesh, double* lds, con
 }
 
 template <int NI, class Grids>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NI == 4 ? 1 : 2, NI == 4 ? 1 : 2))) void pm_trace_lambda_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void pm_trace_lambda_kernel(
     DevCosmo cz, Grids grids, double h_rk, double chi_s, double f_rk, int32_t max_steps, double* rays, int64_t N,
     uint8_t* flags, int32_t* steps_out) {
   __shared__ double lds[PmWave<NI, false>::kDoubles];
