@@ -50,10 +50,10 @@ __global__ void pm_twiddle_kernel(double2* tw, int M) {
   tw[k] = make_double2(c, -s);   // exp(-2 pi i k / M)
 }
 
-__global__ void pm_cic_kernel(const double* __restrict__ xyzm, int64_t np, double ox, double oy, double oz, double h,
-                              int n, int periodic, double* rho) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= np) return;
+// Adds one particle's cloud: add(node, mass) for each of its nodes.
+template <class Add>
+__device__ __forceinline__ void cic_cloud(const double* __restrict__ xyzm, int64_t np, int64_t p, double ox, double oy, double oz,
+                                          double h, int n, int periodic, Add&& add) {
   const double u[3] = {(xyzm[p] - ox) / h, (xyzm[np + p] - oy) / h, (xyzm[2 * np + p] - oz) / h};
   const double m = xyzm[3 * np + p];
   int64_t i0[3];
@@ -75,8 +75,34 @@ __global__ void pm_cic_kernel(const double* __restrict__ xyzm, int64_t np, doubl
       continue;
     }
     const double w = (a ? f[0] : 1.0 - f[0]) * (b ? f[1] : 1.0 - f[1]) * (c ? f[2] : 1.0 - f[2]);
-    atomicAdd(&rho[(i * n + j) * n + k], m * w);
+    add((i * n + j) * n + k, m * w);
   }
+}
+
+__global__ void pm_cic_kernel(const double* __restrict__ xyzm, int64_t np, double ox, double oy, double oz, double h,
+                              int n, int periodic, double* rho) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= np) return;
+  cic_cloud(xyzm, np, p, ox, oy, oz, h, n, periodic, [&](int64_t node, double m) { atomicAdd(&rho[node], m); });
+}
+
+// Grids of at most kCicSmall nodes a side, whose few cache lines of masses every particle's eight additions would meet
+// at: each workgroup adds its particles up in LDS first (10^5 particles, 4^3 nodes, whole build: 868 -> 80 us, 442
+// when the masses lay 16 B apart).
+constexpr int kCicSmall = 8, kCicThreads = 256;
+__global__ __launch_bounds__(kCicThreads) void pm_cic_small_kernel(const double* __restrict__ xyzm, int64_t np, double ox,
+                                                                   double oy, double oz, double h, int n, int periodic,
+                                                                   double* rho) {
+  __shared__ double sum[kCicSmall * kCicSmall * kCicSmall];
+  for (int i = threadIdx.x; i < n * n * n; i += kCicThreads) sum[i] = 0.0;
+  __syncthreads();
+  for (int64_t p = (int64_t)blockIdx.x * kCicThreads + threadIdx.x; p < np; p += (int64_t)gridDim.x * kCicThreads)
+    cic_cloud(xyzm, np, p, ox, oy, oz, h, n, periodic, [&](int64_t node, double m) {
+      __hip_atomic_fetch_add(&sum[node], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    });
+  __syncthreads();
+  for (int i = threadIdx.x; i < n * n * n; i += kCicThreads)
+    if (sum[i] != 0.0) atomicAdd(&rho[i], sum[i]);
 }
 
 // ------------------------------------------------------------------ transforms
@@ -1548,7 +1574,10 @@ hipError_t launch_pm_build(const double* xyzm, int64_t np, double eps, const dou
                        1.0 / (double)M3, 1.0 / len, ps, sz);
   }
   hipLaunchKernelGGL(pm_clear_kernel, dim3(blocks_for(n3, 256)), dim3(256), 0, s, rho, n3);
-  if (np > 0)
+  if (np > 0 && n <= kCicSmall)
+    hipLaunchKernelGGL(pm_cic_small_kernel, dim3(np < 64 * kCicThreads ? blocks_for(np, kCicThreads) : 64u), dim3(kCicThreads), 0,
+                       s, xyzm, np, origin[0], origin[1], origin[2], h, n, periodic, rho);
+  else if (np > 0)
     hipLaunchKernelGGL(pm_cic_kernel, dim3(blocks_for(np, 256)), dim3(256), 0, s, xyzm, np, origin[0], origin[1],
                        origin[2], h, n, periodic, rho);
   const int64_t lines = (int64_t)n * n;
