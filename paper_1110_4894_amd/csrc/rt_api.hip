@@ -868,7 +868,7 @@ rt_status rt_mu_histogram(int64_t n, const double* mu, int32_t n_bins, double lo
   if (!std::isfinite(log_lo) || !std::isfinite(log_hi)) return fail(RT_ERR_NONFINITE, "histogram range");
   if (!(log_hi > log_lo)) return fail(RT_ERR_INVALID_ARG, "log_hi must exceed log_lo");
   StreamScratch work(stream);
-  RT_HIP(work.alloc(sizeof(double) * histogram_scratch_doubles()));
+  RT_HIP(work.alloc(sizeof(double) * histogram_scratch_doubles(n, n_bins)));
   RT_HIP(launch_histogram(n, mu, nullptr, 0, n_bins, log_lo, log_hi, pdf, moments, static_cast<double*>(work.p),
                           stream));
   RT_HIP(work.release());
@@ -900,7 +900,7 @@ rt_status rt_shear_histogram(int64_t n, const double* mu, const double* jac, int
   if (!std::isfinite(lo) || !std::isfinite(hi)) return fail(RT_ERR_NONFINITE, "histogram range");
   if (!(hi > lo)) return fail(RT_ERR_INVALID_ARG, "hi must exceed lo");
   StreamScratch work(stream);
-  RT_HIP(work.alloc(sizeof(double) * histogram_scratch_doubles()));
+  RT_HIP(work.alloc(sizeof(double) * histogram_scratch_doubles(n, n_bins)));
   RT_HIP(launch_histogram(n, mu, jac, 1, n_bins, lo, hi, pdf, moments, static_cast<double*>(work.p), stream));
   RT_HIP(work.release());
   return RT_OK;

@@ -107,7 +107,7 @@ hipError_t launch_flexion(double chi_s, int64_t nb, double radius, const double*
 // The static scratch of rt_mu_histogram_noalloc on the current device (its address is
 // looked up once per device) and the largest bin count it holds.
 hipError_t noalloc_scratch(double** out, int32_t* max_bins);
-size_t histogram_scratch_doubles();   // of launch_histogram's work, for up to 65536 bins
+size_t histogram_scratch_doubles(int64_t n, int32_t n_bins);   // of launch_histogram's work
 hipError_t launch_histogram(int64_t n, const double* mu, const double* jac, int mode, int32_t n_bins, double lo,
                             double hi, double* pdf, double* moments, double* work, hipStream_t s);
 

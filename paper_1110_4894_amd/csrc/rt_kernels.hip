@@ -1292,7 +1292,9 @@ constexpr int kHistStats = 6;          // sum w, sum w v, second moment about th
 constexpr int kHistScratch = 65536 + 8;   // doubles of scratch, whatever the bins
 
 __host__ __device__ inline int hist_parts(int64_t n, int nb) {
-  const int64_t fit = kHistScratch / (nb + kHistStats), want = (n + kHistRow - 1) / kHistRow;
+  // (a quarter of a round each for up to 64 workgroups: 1000 bundles, 200 bins, 15.3 -> 12.3 us)
+  const int64_t fit = kHistScratch / (nb + kHistStats), row = n <= 64 * (kHistRow / 4) ? kHistRow / 4 : kHistRow;
+  const int64_t want = (n + row - 1) / row;
   const int64_t k = fit < kHistParts ? fit : kHistParts;
   return (int)(want < 1 ? 1 : (want < k ? want : k));
 }
@@ -1309,7 +1311,8 @@ __device__ __forceinline__ double sum256(double v, double* sh) {
 
 // bins[id] += w for the wavefront's 64 (id, w), id < 0 for none.  The lanes of equal id are
 // found by ballots over the id's bits; the lowest of them adds the others' weights in lane
-// order and alone touches the bin.
+// order and alone touches the bin.  Few different ids, i.e. many lanes of one: a sum over the wavefront for each
+// (1000 bundles in one bin: 29.9 -> 12.2 us a call).
 __device__ __forceinline__ void wave_bin_add(double* bins, int id, double w, int bits) {
   const int lane = threadIdx.x & 63;
   unsigned long long same = __ballot(id >= 0);
@@ -1319,6 +1322,18 @@ __device__ __forceinline__ void wave_bin_add(double* bins, int id, double w, int
     same &= one ? m : ~m;
   }
   const bool leads = id >= 0 && (same & ((1ull << lane) - 1ull)) == 0;
+  unsigned long long leaders = __ballot(leads);
+  if (__popcll(leaders) <= 3) {
+    for (; leaders != 0; leaders &= leaders - 1) {
+      const int lead = __ffsll(leaders) - 1, its = __builtin_amdgcn_readlane(id, lead);
+      double v = id == its ? w : 0.0;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+      if (lane == lead) bins[its] += v;
+    }
+    wave_sync();
+    return;
+  }
   unsigned long long rest = leads ? same : 0ull;
   double sum = 0.0;
   while (__any(rest != 0)) {
@@ -1342,7 +1357,7 @@ __global__ __launch_bounds__(256) void hist_part_kernel(int64_t n, const double*
   while ((1 << bits) < nb) ++bits;
   for (int i = threadIdx.x; i < 4 * nb; i += 256) bins[i] = 0.0;
   __syncthreads();
-  const int64_t per = (((n + gridDim.x - 1) / gridDim.x + kHistRow - 1) / kHistRow) * kHistRow;
+  const int64_t per = (((n + gridDim.x - 1) / gridDim.x + 255) / 256) * 256;
   const int64_t i0 = (int64_t)blockIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
   double sw = 0.0, swv = 0.0, m2 = 0.0, bad = 0.0, under = 0.0, over = 0.0;
   for (int64_t r0 = i0; r0 < i1; r0 += kHistRow) {
@@ -1352,6 +1367,7 @@ __global__ __launch_bounds__(256) void hist_part_kernel(int64_t n, const double*
       const int64_t i = r0 + 256 * k + threadIdx.x;
       int id = -1;
       w[k] = v[k] = 0.0;
+      if (r0 + 256 * k >= i1) continue;
       if (i < i1) {
         const double m = mu[i];
         if (m > 0.0) {
@@ -1659,7 +1675,9 @@ hipError_t launch_observer_phi(DevCosmo c, const ObsSet* sets, int n_sets, doubl
   return hipGetLastError();
 }
 
-size_t histogram_scratch_doubles() { return kHistScratch; }
+size_t histogram_scratch_doubles(int64_t n, int32_t n_bins) {
+  return n_bins <= kHistParted ? (size_t)hist_parts(n, n_bins) * (n_bins + kHistStats) : (size_t)n_bins + 8;
+}
 
 size_t observer_part_doubles() { return (size_t)kObsFields * kObsParts; }
 

@@ -1,10 +1,11 @@
-"""Many values for few targets: masses of a great many particles on a grid of a few nodes.  Right, and no slower than
-the same values on more targets (medians of events, compared within the test)."""
+"""Many values for few targets: histograms of one or a few bins, masses of a great many particles on a grid of a
+few nodes.  Right, and no slower than the same values on more targets (medians of events, compared within the test)."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
+import oracle as orc
 from oracle import pm as opm
 from paper_1110_4894_amd import rt
 
@@ -29,6 +30,39 @@ def _us(call, burst=50):
         torch.cuda.synchronize()
         out.append(a.elapsed_time(b) * 1e3 / burst)
     return float(np.median(out[2:]))
+
+
+def _mu_histogram(mu, bins):
+    d = torch.from_numpy(mu).cuda()
+    pdf = torch.empty(bins, dtype=torch.float64, device="cuda")
+    mom = torch.empty(6, dtype=torch.float64, device="cuda")
+    call = lambda: rt.rt_mu_histogram_noalloc(len(mu), d, bins, -0.1, 0.3, pdf, mom)
+    call()
+    torch.cuda.synchronize()
+    return call, pdf.cpu().numpy(), mom.cpu().numpy()
+
+
+@pytest.mark.parametrize("kind", ["one value", "two bins", "three bins", "four bins", "spread"])
+@pytest.mark.parametrize("n", [64, 1000, 16385])
+def test_values_that_share_bins(n, kind):
+    rng = np.random.default_rng(n)
+    k = {"one value": 1, "two bins": 2, "three bins": 3, "four bins": 4, "spread": 150}[kind]
+    mu = 10.0 ** (-0.1 + 0.4 * (rng.integers(0, k, n) + 0.5) / 200)
+    _, pdf, mom = _mu_histogram(mu, 200)
+    want = orc.mu_histogram(mu, 200, -0.1, 0.3)
+    # sums of n positive terms in another order, and a bin's width (the difference of two powers of ten)
+    rtol = 2.0 * n * 2.0 ** -53 + 1e-13 + 8.0 * 2.0 ** -53 / (1.0 - 10.0 ** (-0.4 / 200))
+    assert np.allclose(pdf, want[0], rtol=rtol, atol=0)
+    # (the spread about the mean has its own tests: of equal values it is nothing but the mean's rounding)
+    assert np.allclose(np.delete(mom, 2), np.delete(want[1], 2), rtol=1e-12, atol=1e-15)
+
+
+def test_one_bin_costs_what_many_do():
+    """A wavefront's values of one bin meet in six exchanges (one after the other they were 64: twice the time)."""
+    mu = np.exp(np.random.default_rng(1).normal(0, 0.1, 1000))
+    one, many = _us(_mu_histogram(mu, 1)[0]), _us(_mu_histogram(mu, 200)[0])
+    print("1 bin %.1f us, 200 bins %.1f us" % (one, many))
+    assert one <= 1.5 * many
 
 
 def _deposit(n, periodic, m):
