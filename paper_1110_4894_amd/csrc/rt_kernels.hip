@@ -1267,8 +1267,8 @@ __device__ __forceinline__ double hist_value(int mode, const double* mu, const d
 __device__ __forceinline__ int value_bin(double v, double lo, double hi, int nb) {
   if (v < lo) return -1;
   if (v >= hi) return nb;
-  int i = (int)floor((v - lo) / (hi - lo) * nb);
-  return i >= nb ? nb - 1 : i;
+  const double f = floor((v - lo) / (hi - lo) * nb);
+  return f >= 1.0 ? (f < nb ? (int)f : nb - 1) : 0;   // (no number: the first bin.  The result is an index into LDS)
 }
 
 template <int NT>

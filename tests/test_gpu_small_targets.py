@@ -101,3 +101,22 @@ def test_few_nodes_cost_what_more_do(periodic):
     few, more = _us(_deposit(4, periodic, 100000)[0], 5), _us(_deposit(16, periodic, 100000)[0], 5)
     print("4^3 nodes %.0f us, 16^3 nodes %.0f us" % (few, more))
     assert few <= 1.5 * more
+
+
+@pytest.mark.parametrize("bins", [1, 7, 1024, 1025])
+def test_shear_that_is_no_number_counts_in_the_first_bin(bins):
+    """mu and the Jacobian are independent arrays: a weight with no value has a bin all the same, on both ways."""
+    n = 777
+    rng = np.random.default_rng(bins)
+    mu, jac = np.exp(rng.normal(0, 0.1, n)), rng.normal(0, 0.02, (4, n))
+    lost = rng.random(n) < 0.1
+    jac[1, lost] = np.nan
+    pdf, mom = torch.empty(bins, dtype=torch.float64, device="cuda"), torch.empty(6, dtype=torch.float64, device="cuda")
+    rt.rt_shear_histogram(n, torch.from_numpy(mu).cuda(), torch.from_numpy(jac).cuda(), bins, 0.0, 0.1, pdf, mom)
+    torch.cuda.synchronize()
+    jac[1:3, lost] = 0.0   # a value in the first bin
+    want = orc.shear_histogram(mu, jac, bins, 0.0, 0.1)
+    got = mom.cpu().numpy()
+    assert np.allclose(pdf.cpu().numpy(), want[0], rtol=1e-12, atol=0)
+    assert np.isclose(got[0], want[1][0], rtol=1e-12) and np.isnan(got[1]) and np.isnan(got[2])
+    assert np.array_equal(got[3:], want[1][3:])
