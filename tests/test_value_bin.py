@@ -36,7 +36,7 @@ def test_every_value_has_a_defined_bin(tmp_path):
     with open(os.path.join(ROOT, "paper_1110_4894_amd", "csrc", "rt_kernels.hip")) as f:
         body = re.search(r"__device__ __forceinline__ (int value_bin\(.*?\n\})", f.read(), re.S).group(1)
     src, exe = tmp_path / "bin.cpp", tmp_path / "bin"
-    src.write_text("#include <cmath>\n#include <cstdio>\nusing std::floor;\nstatic " + body + MAIN)
+    src.write_text("#include <cmath>\n#include <cstdio>\n#include <initializer_list>\nusing std::floor;\nstatic " + body + MAIN)
     subprocess.run([gxx, "-std=c++17", "-O1", "-fsanitize=undefined,float-cast-overflow", "-fno-sanitize-recover=all",
                     str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
