@@ -117,6 +117,7 @@ rt_status rt_replica_step_sets(const double* nodes, int32_t n_steps, double box,
  * E0 = 1 + 2 phi_obs, F0 = 1 - 2 phi_obs so that the wave vector is exactly null, phi_obs
  * being the potential at the observer of the field's step-0 set (0 for bundles outside every
  * field or when that step has no set).
+ * Not while `stream` is being captured, unless no field has a set at step 0 (RT_ERR_DEVICE, nothing enqueued).
  * theta: device [2][n_bundles] radians; rays: device [8][9 n_bundles] output.
  * fields: host [n_fields] (may be NULL when n_fields == 0).  radius: radians, 0 < radius < 1e-2. */
 rt_status rt_build_bundles(const rt_cosmology* cosmo, const rt_field* fields, int32_t n_fields,

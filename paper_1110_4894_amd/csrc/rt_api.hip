@@ -714,6 +714,13 @@ rt_status rt_build_bundles(const rt_cosmology* cosmo, const rt_field* fields, in
       need.push_back(f);
       covered += fields[f].n_bundles;
     }
+  if (!need.empty()) {
+    // the scratch below would become part of the caller's graph, as memory that only one launch of it at a time may hold
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    RT_HIP(hipStreamIsCapturing(stream, &cap));
+    if (cap != hipStreamCaptureStatusNone)
+      return fail(RT_ERR_DEVICE, "rt_build_bundles with a set at a field's first step: the stream is being captured");
+  }
   // bundles of no such field see phi = 0 (the fields' slices do not overlap)
   if (covered < n_bundles) RT_HIP(launch_bundles(dc, nullptr, 0, n_bundles, n_bundles, theta, radius, rays, stream));
   if (need.empty()) return RT_OK;
