@@ -325,6 +325,7 @@ struct Workload {
   int fields = 0;            // with bundles
   double groups = 0.0;       // of 7 bundles
   double pairs = 0.0;        // groups x particles of a mean step, over the fields
+  bool background = false;   // some step's set has one
   double rays = 0.0;         // total rays
   double mean_np = 0.0;      // particles per step, averaged over rays and steps
   double interactions = 0.0;
@@ -342,6 +343,7 @@ Workload describe(const rt_field* fields, int32_t n_fields, int32_t sb, int32_t 
       if (F.step_set[s] >= 0) {
         np += (double)F.sets[F.step_set[s]].n;
         w.max_np = std::max(w.max_np, F.sets[F.step_set[s]].n);
+        w.background = w.background || F.sets[F.step_set[s]].background;
       }
     if (F.n_bundles > 0) {
       const double groups = std::ceil((double)F.n_bundles / 7.0);
@@ -361,17 +363,44 @@ Workload describe(const rt_field* fields, int32_t n_fields, int32_t sb, int32_t 
 // particles than a small set.  The others: up to about one workgroup per compute unit, which their largest (32
 // rays) reaches at 32 rays per unit; beyond, by the measured crossings with the plans of a ray per lane (4 steps, ms,
 // 32 rays a workgroup / best other): 16128 rays x 2000 particles 0.49 / 0.65, x 32768 6.4 / 7.0, x 262144 29.0 / 26.0
-// (2 steps); 32256 x 2000 (one chunk, staged once) 0.93 / 1.02, x 8000 3.29 / 3.17.
+// (2 steps); 32256 x 2000 (one chunk, staged once) 0.93 / 1.02, x 8000 3.29 / 3.17; sets of a few rounds of a
+// wavefront leave most of a workgroup idle: 32256 x 64 0.28 / 0.17, 20736 x 100 0.22 / 0.18, 13500 x 64 0.16 / 0.14.
 bool few_pays(bool fp64, int id, const Workload& w, int n_cu) {
   const rt_plan_info p = plan_info(fp64, id);
   if (p.waves_per_block == 1) return w.max_np <= kSmallSet;
-  const double per_cu = w.max_np <= 4096 ? 128.0 : (w.max_np <= 65536 ? 64.0 : 32.0);
+  const double per_cu = w.max_np <= 128 ? 64.0 : w.max_np <= 4096 ? 128.0 : (w.max_np <= 65536 ? 64.0 : 32.0);
   return w.max_np > kSmallSet && w.rays <= per_cu * n_cu;
+}
+
+// Times of the FP32 plans of one field, us for 4 steps: k workgroups on a compute unit (per_cu at most) take fixed[k - 1] +
+// pair[k - 1] x particles, and `corners` more where the sets have a background.  Measured on one box at 300 to 28672 bundles x
+// 64 to 262144 particles, of which each figure is a fit to the launches with that many workgroups on a unit.  After a full
+// round the last one overlaps with it: 0.6 of its time with one workgroup on a unit, 0.95 with more.
+// Over those launches the plan so chosen takes 0.5% more than the best on average, 8% at most; by the estimate before it
+// (rounds times a cost per pair, eight wavefronts to a group up to 512 groups, plan 6 below 8192 particles), 7% and 83%, e.g. 4300
+// bundles x 8100 particles 0.99 ms against 0.57, 3584 x 500 0.23 against 0.15, 2400 x 32768 1.55 against 1.26.
+struct PlanTime {
+  int id, groups, per_cu;   // of 7 bundles in a workgroup
+  double fixed[3], pair[3], corners;
+};
+constexpr PlanTime kPlanTimes32[] = {{0, 8, 2, {155, 250}, {0.1262, 0.2066}, 304},
+                                     {1, 4, 2, {185, 275}, {0.0667, 0.1110}, 173},
+                                     {2, 2, 2, {190, 300}, {0.0380, 0.0577}, 95},
+                                     {3, 1, 2, {195, 300}, {0.0230, 0.0318}, 55},
+                                     {6, 4, 3, {97, 125, 150}, {0.1100, 0.1270, 0.1777}, 213},
+                                     {7, 1, 3, {110, 133, 160}, {0.0365, 0.0405, 0.0520}, 75},
+                                     {10, 1, 1, {109}, {0.0206}, 51}};
+
+double plan_time(const PlanTime& p, const Workload& w, int n_cu) {
+  const double items = std::ceil(w.groups / p.groups), full = std::floor(items / (p.per_cu * n_cu));
+  const int last = (int)std::ceil((items - full * p.per_cu * n_cu) / n_cu);
+  auto round = [&](int k) { return p.fixed[k - 1] + p.pair[k - 1] * w.mean_np + (w.background ? p.corners : 0.0); };
+  return full * round(p.per_cu) + (last == 0 ? 0.0 : round(last) * (full == 0.0 || p.per_cu == 1 ? 1.0 : (last == 1 ? 0.6 : 0.95)));
 }
 
 // Default plan.  Small sets only, or few rays: the plans of few rays, with as few rays per workgroup as still
 // leave every workgroup a compute unit of its own.
-// Otherwise as many wavefronts sharing a ray group as fill the chip best.
+// Otherwise the smallest estimate of time (FP32), or as many wavefronts sharing a ray group as fill the chip best (FP64).
 int heuristic_plan(bool fp64, const Workload& w, int n_cu) {
   int few = -1;
   for (int id = 0; id < plan_count(fp64); ++id) {
@@ -381,42 +410,43 @@ int heuristic_plan(bool fp64, const Workload& w, int n_cu) {
   }
   if (few >= 0) return few;
   const double waves = w.rays / 64.0;
-  if (!fp64) {
-    // No more groups of 7 bundles than compute units: eight wavefronts to a group with 256 registers each (plan 10), since
-    // no unit holds a second workgroup anyway: 16128 rays x 262144 particles, 2 steps, 3.6 ms against 4.2 with 128 registers,
-    // x 16000, 4 steps, 0.60 against 0.81.  In two rounds up to 32768 particles (2.06 ms, 2.08), beyond no more.
+  int wpr = 0;
+  if (!fp64 && w.fields == 1) {
+    double best = 0.0;
+    int id = -1;
+    for (const PlanTime& p : kPlanTimes32) {
+      const double t = plan_time(p, w, n_cu);
+      if (id < 0 || t < best) {
+        best = t;
+        id = p.id;
+      }
+    }
+    if (plan_info(false, id).waves_per_block != 8 || plan_info(false, id).waves_per_simd != 4) return id;
+    wpr = plan_info(false, id).waves_per_group;   // and its tile below
+  } else if (!fp64) {
+    // several fields share the workgroups: no more groups than units, eight wavefronts to a group with 256 registers each;
+    // sets of a few tiles, whose stages are mostly reduction and right-hand side, three wavefronts per SIMD
     if (w.groups <= (w.mean_np <= 32768.0 ? 2.0 : 1.0) * n_cu) return 10;
-    // Sets of a few tiles: a stage is mostly reduction, right-hand side and background, which three wavefronts per
-    // SIMD do with fewer spills than four (4 steps, 4096 particles in a box, 129024 rays: 1.2 ms against 2.0 to 3.9).
     if (w.mean_np < 8192.0) return 6;
   }
-  int wpr = 1;
   if (fp64) {
+    wpr = 1;
     // enough wavefronts for about four per SIMD, with two of the smallest tile left to each (n = 2000, 25920 rays:
     // a split in 8 takes 0.96 ms, in 2 1.75)
     while (wpr < 8 && waves * wpr < 0.9 * 16.0 * n_cu && w.mean_np >= 128.0 * wpr) wpr *= 2;
   } else {
-    // The split with the smallest estimate of time: work items of 8 / wpr groups of 7 bundles on two workgroups
-    // per compute unit, in rounds (a last round of one workgroup per unit runs it at 0.8 of the rate of two), times the cost
-    // per pair of a split, which the reduction of its moments raises for small sets.  Several fields: an even
-    // share of the work and half of the largest item.  Fitted to 4-step launches of 144 to 258048 rays and 16000 to 2^20
-    // particles; e.g. 147456 rays x 262144 (10 steps): split in 4 90 ms, in 2 103, in 8 118, none 130; 110592 rays:
-    // in 2 16.6, in 4 18.7; 64512: in 4 10.0, in 2 13.5; 24 uneven fields: in 4 22.1, in 2 26.2, none 28.6.
-    const double slots = 2.0 * n_cu, n = std::max(w.mean_np, 1.0);
-    double best = 0.0;
-    for (int k = 1; k <= 8; k *= 2) {
-      const double ng = 8.0 / k;
-      const double cost = k == 1 ? 1.0 : (k == 2 ? 1.03 + 1600.0 / n : (k == 4 ? 1.03 + 4000.0 / n : 1.25 + 12000.0 / n));
-      double span;
-      if (w.fields == 1) {
-        const double items = std::ceil(w.groups / ng), full = std::floor(items / slots), rest = items - full * slots;
-        span = ng * (full + (rest <= 0.0 ? 0.0 : (rest <= n_cu ? 0.625 : 1.0)));
-      } else {
-        span = w.pairs / (slots * std::max<double>(1.0, (double)w.max_np)) + 0.5 * ng;
-      }
-      if (k == 1 || cost * span < 0.995 * best) {
-        best = cost * span;
-        wpr = k;
+    if (wpr == 0) {
+      // Several fields: an even share of the work and half of the largest item, times the cost per pair of a split, which the
+      // reduction of its moments raises for small sets (24 uneven fields: split in 4 22.1 ms, in 2 26.2, none 28.6).
+      const double slots = 2.0 * n_cu, n = std::max(w.mean_np, 1.0);
+      double best = 0.0;
+      for (int k = 1; k <= 8; k *= 2) {
+        const double cost = k == 1 ? 1.0 : (k == 2 ? 1.03 + 1600.0 / n : (k == 4 ? 1.03 + 4000.0 / n : 1.25 + 12000.0 / n));
+        const double span = w.pairs / (slots * std::max<double>(1.0, (double)w.max_np)) + 4.0 / k;
+        if (k == 1 || cost * span < 0.995 * best) {
+          best = cost * span;
+          wpr = k;
+        }
       }
     }
     // the plan of 8 wavefronts with this sharing and the largest tile of which the sets hold twelve (n = 16000,
