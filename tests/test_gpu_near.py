@@ -125,3 +125,21 @@ def test_rays_that_leave_the_expansion_points():
     rt.rt_force_plan(FP32K, -1)
     print("planes kept %.2f ms, rays moved %.2f ms" % (kept, moved))
     assert moved <= 3.0 * kept
+
+
+@pytest.mark.parametrize("order", ["random", "sorted"])
+def test_full_lists_give_the_rays_of_one_run(order):
+    """Step windows of any width give the same bits as one launch: a second visit's walk through the tiles repeats the
+    first's, and a visit that cannot reuse the plane sums what a launch that starts there would."""
+    xyz, m = _filament(9001, order, heavy=1e6)
+    case = Case(xyz, 1e9 * m, 28, 3e-5, 0.0005, 6)
+    for plan in range(rt.rt_plan_count(FP32K)):
+        rt.rt_force_plan(FP32K, plan)
+        whole = case.trace(FP32K)
+        for width in (1, 4):
+            case.rays.copy_(case.first)
+            for s in range(1, 7, width):
+                rt.rt_trace(case.c, ZS, case.table, FP32K, s, min(s + width, 7), case.nb, case.rays)
+            torch.cuda.synchronize()
+            assert np.array_equal(case.rays.cpu().numpy(), whole), (plan, width)
+    rt.rt_force_plan(FP32K, -1)
