@@ -1086,7 +1086,8 @@ __global__ __launch_bounds__(kObsThreads) void observer_partial_kernel(ObsSets s
   if (threadIdx.x == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// The partial sums of a set in a fixed order, and its cuboid background.
+// The partial sums of a set in a fixed order, and its cuboid background, a corner to a lane (one after the other the
+// eight were most of this kernel's 8 us).
 __global__ __launch_bounds__(64) void observer_final_kernel(DevCosmo c, ObsSets sets, int n_part, const double* part,
                                                             double* phi) {
   const ObsSet& s = sets.s[blockIdx.x];
@@ -1094,15 +1095,11 @@ __global__ __launch_bounds__(64) void observer_final_kernel(DevCosmo c, ObsSets 
   for (int k = threadIdx.x; k < n_part; k += 64) acc += part[(int64_t)blockIdx.x * n_part + k];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (threadIdx.x == 0) {
-    double p = -c.G * acc;
-    if (s.background) {
-      double U, ux, uy, uz;
-      cuboid_field(s.lo, s.hi, 0.0, 0.0, 0.0, U, ux, uy, uz);
-      p += c.G_rho * U;
-    }
-    phi[blockIdx.x] = p;
-  }
+  double u[4] = {0.0, 0.0, 0.0, 0.0};
+  if (s.background && threadIdx.x < 8) cuboid_corner(s.lo, s.hi, threadIdx.x, 0.0, 0.0, 0.0, u[0], u[1], u[2], u[3]);
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) u[0] += __shfl_xor(u[0], off);
+  if (threadIdx.x == 0) phi[blockIdx.x] = -c.G * acc + c.G_rho * u[0];
 }
 
 // One thread per ray; the bundles of [b0, b0 + nb_range) share the potential at the observer.
