@@ -398,6 +398,34 @@ double plan_time(const PlanTime& p, const Workload& w, int n_cu) {
   return full * round(p.per_cu) + (last == 0 ? 0.0 : round(last) * (full == 0.0 || p.per_cu == 1 ? 1.0 : (last == 1 ? 0.6 : 0.95)));
 }
 
+// FP64, more rays than one round of the plans of few rays holds (32 rays on every compute unit): the smallest of their times
+// and that of a split in eight of a ray group.  us for 4 steps: a round of few rays takes round + pair x particles, less a pair
+// where the set stays in LDS, and fixed besides.  Fits as above, to launches of 914 to 3638 bundles x 64 to 262144 particles: the
+// plan so chosen is within 1% of the best on average and 8% at most (15% where the split's last round holds a workgroup or two,
+// 3585 to 3640 bundles); 32 rays in as many rounds as it takes, the rule before, 13% and 60%, and longer than the split that it
+// had replaced: 928 bundles x 63138 particles 6.3 ms, the split 6.1, 16 rays 5.2 (2 steps); 3000 x 200 0.30, 0.19, 0.48.
+struct FewTime {
+  int id;
+  double fixed, round, pair_held, pair, corners;
+};
+constexpr FewTime kFewTimes64[] = {{7, 40, 58, 0.0170, 0.0345, 17}, {8, 38, 54, 0.0380, 0.0550, 24}, {9, 36, 50, 0.0790, 0.0965, 26}};
+constexpr PlanTime kSplitTime64 = {3, 1, 2, {98, 120}, {0.188, 0.342}, 300};
+
+int plan_of_rounds64(const Workload& w, int n_cu) {
+  int id = kSplitTime64.id;
+  double best = plan_time(kSplitTime64, w, n_cu);
+  for (const FewTime& p : kFewTimes64) {
+    const rt_plan_info info = plan_info(true, p.id);
+    const double pair = (w.max_np <= info.tile ? p.pair_held : p.pair) * w.mean_np;
+    const double t = p.fixed + std::ceil(w.rays / ((double)info.rays_per_block * n_cu)) * (p.round + pair + (w.background ? p.corners : 0.0));
+    if (t < best) {
+      best = t;
+      id = p.id;
+    }
+  }
+  return id;
+}
+
 // Default plan.  Small sets only, or few rays: the plans of few rays, with as few rays per workgroup as still
 // leave every workgroup a compute unit of its own.
 // Otherwise the smallest estimate of time (FP32), or as many wavefronts sharing a ray group as fill the chip best (FP64).
@@ -408,7 +436,10 @@ int heuristic_plan(bool fp64, const Workload& w, int n_cu) {
     few = id;   // in ascending order of rays per workgroup
     if (w.rays <= (double)plan_info(fp64, id).rays_per_block * n_cu) break;
   }
-  if (few >= 0) return few;
+  if (few >= 0) {
+    const rt_plan_info p = plan_info(fp64, few);
+    return p.waves_per_block == 1 || w.rays <= (double)p.rays_per_block * n_cu ? few : plan_of_rounds64(w, n_cu);
+  }
   const double waves = w.rays / 64.0;
   int wpr = 0;
   if (!fp64 && w.fields == 1) {
