@@ -77,8 +77,10 @@ FLOP_FP64 = 20.0
 # one 25-step window of the 2^20 box), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a
 # plain copy kernel, keyed by trace_kernel_code_sha of the kernel they were taken on.
 MEASURED_TRAFFIC = {
-    # trace_kernel<false, 8, 4, 576, 4>: FETCH_SIZE 84998600.4 KiB x 1.9999, WRITE_SIZE 18092042.8 KiB x 1.0
-    "27a21884c7f3b010": {"read": 174068429839.3, "write": 18526251776.0, "plan": 2},
+    # trace_kernel<false, 8, 1, 2304, 4>: FETCH_SIZE 17647130.4 KiB x 1.9999, WRITE_SIZE 3180735.8 KiB x 1.0
+    "65aaab58fb369a50": {"read": 36139516069.8, "write": 3257073472.0, "plan": 8},
+    # trace_kernel<false, 8, 4, 576, 4>: FETCH_SIZE 103944318.2 KiB x 1.9999, WRITE_SIZE 12899191.2 KiB x 1.0
+    "7ff1e14abbaa2fc1": {"read": 212867319877.8, "write": 13208771776.0, "plan": 2},
 }
 
 

@@ -143,11 +143,11 @@ rt_status rt_build_bundles(const rt_cosmology* cosmo, const rt_field* fields, in
  * over tiles); each ray assembles its field in FP64 from the moments and its own offset (Sec.
  * 3.1: the ring-minus-anchor differences keep FP32 relative precision).  Pairs closer than 1024
  * times the bundle's largest ray offset are summed per ray directly in FP64; the truncation of
- * the expansion stays below 6e-6 of each pair's ring difference.  A plane z that two stages visit
+ * the expansion stays below 7e-6 of each pair's ring difference.  A plane z that two stages visit
  * (a step's second and third; its fourth and the next step's first) is summed once: the second
  * visit assembles its fields from the first one's moments and its own offsets wherever those pass
- * the same nearness test.  Particle positions are held as two FP32 parts.  A set whose masses are all equal (checked on the device at every call) skips
- * the per-pair mass product.  Sets of at most 63 particles (point lenses) are summed per ray
+ * the same nearness test.  Particle positions are held as two FP32 parts.  A set whose masses
+ * are all equal (checked on the device at every call) skips the per-pair mass product.  Sets of at most 63 particles (point lenses) are summed per ray
  * directly in FP64.
  * rays: device [8][9 n_bundles], updated in place.  ray_flags: device [9 n_bundles] or NULL;
  * bits are OR-ed in: 1 non-finite state, 2 kz <= 0 (ray turned back), 4 |phi|/a > 1e-2 (outside
@@ -335,8 +335,9 @@ rt_status rt_autotune(const rt_cosmology* cosmo, double z_source, const rt_field
 typedef struct rt_trace_info {
   double kernel_ms;           /* time of the trace kernel of the last rt_trace (HIP events on its
                                  stream; 0 unless timing is enabled)                           */
-  double interactions;        /* ray-particle pair terms evaluated: sum over fields of
-                                 rays x 4 stages x particles of each step                      */
+  double interactions;        /* ray-particle pair terms of the direct sum: sum over fields of
+                                 rays x 4 stages x particles of each step.  RT_FP32_KAHAN takes
+                                 a pair once for nine rays, and a plane's two visits at once   */
   int32_t plan_id;            /* plan used                                                     */
   int32_t grid_blocks;        /* workgroups launched (persistent)                             */
   int32_t n_items;            /* work items (field, ray block)                                 */

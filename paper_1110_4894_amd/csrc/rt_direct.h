@@ -100,8 +100,8 @@ __device__ __forceinline__ void pair_fp64(const double4 c, double x, double y, d
 // workgroup and stage, FP64 issue of the workgroup's compute unit.  Registers: two wavefronts per SIMD, so
 // that the ray state stays in them (the other plans' 128 per lane spill it, and at one or two
 // wavefronts per SIMD nothing hides the reloads).
-// Measured: a point lens's 1024 bundles through 1225 steps 24.4 -> 3.7 ms (0.8 us a stage); 49 bundles in a halo of
-// 3001 particles 103 -> 5.1 ms; 4 steps of 16 bundles, 32768 particles 6.7 -> 0.8 ms; of 896 bundles 6.8 -> 3.3 ms.
+// Measured: a point lens's 1024 bundles through 1225 steps 24.4 -> 3.8 ms (0.8 us a stage); 49 bundles in a halo of
+// 3001 particles 103 -> 4.8 ms; 4 steps of 16 bundles, 32768 particles 6.7 -> 0.8 ms; of 896 bundles 6.8 -> 3.3 ms.
 // One pair per particle read (K = 1) took 2.9 ms for 448 bundles against 2.0: LDS could not feed the pairs.
 // ---------------------------------------------------------------------------
 template <int R, int K, int NW, int C>

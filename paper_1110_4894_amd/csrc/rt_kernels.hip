@@ -77,8 +77,9 @@ __device__ __forceinline__ int lane_segment(int lane) { return lane < kLanes ? l
 // pair's field and 5/16 u^3 of its potential, i.e. about 1.5 u^2 and 0.6 u^2 of
 // the pair's ring-minus-anchor difference (its first-order term).  A pair is
 // summed this way only when sqrt(s) >= 1024 |delta|max of its bundle
-// (|u| < 0.002: the neglected terms stay below 6e-6 of the pair's ring
-// difference and 1e-8 of the pair term); closer pairs, and pairs within 1e-4
+// (|u| < 0.002: the neglected terms stay below 7e-6 of the pair's ring
+// difference, the expansion point's own distance from the anchor included, and
+// 1e-8 of the pair term); closer pairs, and pairs within 1e-4
 // Mpc of the expansion point (where s^-7/2 would leave the FP32 range), are
 // left out of the moments and summed per ray directly in FP64.  Softened sets
 // whose softening exceeds 1024 |delta|max for every bundle of a wavefront
@@ -488,8 +489,8 @@ __device__ __forceinline__ void small_set_fp64(const DevCosmo& c, const DevSet& 
 //     kpc, where the anchors of the two visits differ by about 1e-8 Mpc), and thresholds are
 //     rounded up to 5 bits of mantissa.
 // Measured, against a sum at every stage: 28672 bundles x 2^20 particles x 8 steps 752 -> 435 ms,
-// 16384 x 2^18 x 10 172 -> 97.5 ms (87.5 with the staging of stage_tile and the choice of split), 7168 bundles of a
-// 1e5-particle halo x 8 33.4 -> 18.9 ms (14.7 with the near list filled in the moment loop).
+// 16384 x 2^18 x 10 172 -> 97.5 ms (85.6 with the staging of stage_tile, the choice of split and fewer spills), 7168 bundles of a
+// 1e5-particle halo x 8 33.4 -> 18.9 ms (13.5 with the near list filled in the moment loop and fewer spills).
 // Next to no end plane of the 2^20 box's first 25 steps is summed twice (1.534e12 pairs counted, 51 planes
 // hold 1.533e12), about one of ten further on; the error of mu against
 // FP64 is that of before or lower (halo 1.0e-7 for 1.3e-7 at most, box 1.6e-7 for 1.6e-7).
@@ -1061,7 +1062,7 @@ __constant__ double kRingSin[8] = {0.0, 0.70710678118654752440, 1.0, 0.707106781
 // lane sums its own particles (FP64, coalesced columns), each workgroup leaves one partial sum.
 // Bound: one read of the particles (32 B each).  A field_eval_kernel launch has one lane
 // per point, so that a single point left one workgroup to walk the set: rt_build_bundles of 512^2 bundles
-// in front of 2^20 particles took 55.5 ms, and takes 64 us (38 us at the rate of a copy).
+// in front of 2^20 particles took 55.5 ms, and takes 54.5 us (38 us at the rate of a copy).
 constexpr int kObsFields = 32;       // by value in the kernel's arguments (a table there needs no copy and no wait)
 constexpr int kObsParts = 512;       // workgroups per set at most: two per compute unit
 constexpr int kObsThreads = 256;

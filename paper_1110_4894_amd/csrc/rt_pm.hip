@@ -1021,8 +1021,9 @@ __device__ __forceinline__ void pm_gather_lanes(bool want, const PmPoint<NI>& p,
 // Bound: issue and latency of FP64 operations at one to two wavefronts per SIMD.  One ray per lane
 // with its own loads fetched the same lines at every stage (about 130 MB a stage for a band of 7168
 // bundles, 16 B used of each 128 B line) and solved 4 (m + 1) tridiagonal systems: 85.4 ms for that band
-// through 2236 steps against 19.5, and 162 ms against 39.4 for 8192 bundles through 14 periodic 128^3
-// meshes in lambda (21.5 and 43.8 when every stage elected a leader instead of comparing with the kept window).  The fetch shared by the bundle but not kept: 57 and 65 ms.
+// through 2236 steps against 19.5, and 162 ms against 37.1 for 8192 bundles through 14 periodic 128^3
+// meshes in lambda (21.5 and 43.8 when every stage elected a leader instead of comparing with the kept window).
+// The fetch shared by the bundle but not kept: 57 and 65 ms.
 template <int NI, bool SAMEZ>
 struct PmWave {
   static constexpr int m = 2 * NI;
@@ -1233,8 +1234,8 @@ struct PmLanes {
 };
 
 // Whether some bundle of the wavefront becomes wide on straight lines to z_end: a ray more than a twentieth of a
-// node spacing h (for windows of two nodes a side, whose loads are few, a thousandth) away from its anchor.  Its rays then ask for different windows at many stages, and a round of
-// fetching for each takes longer than a load of every ray's own nodes: the wavefront takes that way from the start.
+// node spacing h (for windows of two nodes a side, whose loads are few, a thousandth) away from its anchor.  Its rays
+// then ask for different windows at many stages, and a round of fetching for each takes longer than a load of every ray's own nodes: the wavefront takes that way from the start.
 // Both give a ray the same bits in z.  4096 bundles through a periodic 128^3 mesh, four nodes a side, 40 steps in z, rings of a
 // fifteenth, two thirds and seven spacings: shared 2.3, 4.6, 11.2 ms, own nodes 1.6, 2.2, 8.5; of a 150th 1.9 and 2.9.
 template <int NI>
