@@ -1,5 +1,5 @@
-"""The launch that bench.py times by default, on the plans next to the one that its autotuner picks (one wavefront to a
-group of seven bundles, which runs 3% faster): two and four wavefronts to a group.  Seeded bundles of the band against the oracle
+"""The launch that bench.py times by default, on the plans beside the one of a wavefront to a group of seven bundles: four
+wavefronts to a group, which its autotuner picks on some cards (within 3% of it), and two.  Seeded bundles of the band against the oracle
 traced through the window's first steps: positions and directions, each relative to its change from the straight ray."""
 import dataclasses
 
